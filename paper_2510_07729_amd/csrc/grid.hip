@@ -256,6 +256,263 @@ hipError_t launch_point_order(const ProbeGrid& g, const float* pts, int64_t N,
 // ------------------------------------------------------------------------------------------
 // k nearest probes
 // ------------------------------------------------------------------------------------------
+// A search grows a box of grid cells around its points by one cell a side at a time (the
+// points' own cells and their neighbours first) and stops when the K-th best squared
+// distance is below that to the nearest cell outside the box. One load per lane fetches the
+// ranges of 64 cells of the box, cells that are further off than the K-th best are dropped,
+// and the probes of the rest are numbered across the lanes and fetched 64 at a time: two
+// dependent loads for every 64 cells and 64 probes, where a thread that walks the cells of
+// its own point pays two for every cell (it took 85-117 us, whatever the point count).
+template <int CTRL, int BANKS = 0xF>
+__device__ __forceinline__ uint64_t dpp_u64(uint64_t old, uint64_t v) {
+  const int lo = __builtin_amdgcn_update_dpp((int)(uint32_t)old, (int)(uint32_t)v, CTRL, 0xF,
+                                             BANKS, false);
+  const int hi = __builtin_amdgcn_update_dpp((int)(uint32_t)(old >> 32), (int)(uint32_t)(v >> 32),
+                                             CTRL, 0xF, BANKS, false);
+  return ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo;
+}
+
+// the key of lane l ^ X of the same row of 16 (X = 1, 2, 4, 8), or of its mirror image in a
+// group of X + 1 lanes (X = 3, 7, 15)
+template <int X>
+__device__ __forceinline__ uint64_t row_partner(uint64_t v) {
+  if constexpr (X == 1) return dpp_u64<0xB1>(v, v);
+  else if constexpr (X == 2) return dpp_u64<0x4E>(v, v);
+  else if constexpr (X == 3) return dpp_u64<0x1B>(v, v);
+  else if constexpr (X == 7) return dpp_u64<0x141>(v, v);
+  else if constexpr (X == 15) return dpp_u64<0x140>(v, v);
+  else if constexpr (X == 8) return dpp_u64<0x128>(v, v);
+  else return dpp_u64<0x114, 0xA>(dpp_u64<0x104, 0x5>(v, v), v);   // 4: shift by 4 either way
+}
+
+// one step of a sorting network over the lanes of a row: the lane whose bit BIT is clear
+// keeps the smaller key
+template <int X, int BIT>
+__device__ __forceinline__ uint64_t row_step(uint64_t v, int lane) {
+  const uint64_t o = row_partner<X>(v);
+  return ((o < v) != ((lane & BIT) != 0)) ? o : v;
+}
+
+__device__ __forceinline__ uint64_t row_sort(uint64_t v, int lane) {
+  v = row_step<1, 1>(v, lane);
+  v = row_step<3, 2>(v, lane);
+  v = row_step<1, 1>(v, lane);
+  v = row_step<7, 4>(v, lane);
+  v = row_step<2, 2>(v, lane);
+  v = row_step<1, 1>(v, lane);
+  v = row_step<15, 8>(v, lane);
+  v = row_step<4, 4>(v, lane);
+  v = row_step<2, 2>(v, lane);
+  return row_step<1, 1>(v, lane);
+}
+
+// the 16 smallest keys of two sorted rows, sorted
+__device__ __forceinline__ uint64_t row_merge(uint64_t a, uint64_t b, int lane) {
+  const uint64_t o = row_partner<15>(b);
+  uint64_t v = o < a ? o : a;
+  v = row_step<8, 8>(v, lane);
+  v = row_step<4, 4>(v, lane);
+  v = row_step<2, 2>(v, lane);
+  return row_step<1, 1>(v, lane);
+}
+
+__device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int o) {
+  const uint32_t lo = __shfl_xor((uint32_t)v, o), hi = __shfl_xor((uint32_t)(v >> 32), o);
+  return ((uint64_t)hi << 32) | lo;
+}
+
+// the 16 smallest of the wavefront's 64 keys and of the list `best` (sorted, one copy in
+// every row of 16 lanes): the new list
+__device__ __forceinline__ uint64_t list_merge(uint64_t best, uint64_t key, int lane) {
+  key = row_sort(key, lane);
+  key = row_merge(key, shfl_xor_u64(key, 16), lane);
+  key = row_merge(key, shfl_xor_u64(key, 32), lane);
+  return row_merge(best, key, lane);
+}
+
+// inclusive sum over the lanes (all 64 active)
+__device__ __forceinline__ int wave_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // row 15 -> next row
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // lane 31 -> rows 2, 3
+  return v;
+}
+
+// largest value over the lanes (all 64 active)
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+  auto step = [](uint32_t x, int moved) { return max(x, (uint32_t)moved); };
+  v = step(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0xB1, 0xF, 0xF, false));
+  v = step(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x4E, 0xF, 0xF, false));
+  v = step(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x141, 0xF, 0xF, false));
+  v = step(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x140, 0xF, 0xF, false));
+  v = step(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x142, 0xA, 0xF, false));
+  v = step(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x143, 0xC, 0xF, false));
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// A box of cells [lo, hi] of the search and the box inside it that was visited before
+// (empty at first: lo > hi); ql, qh bound the lattice positions of the points searched for.
+// All wave-uniform.
+struct CellBox {
+  int lo[3], hi[3], plo[3], phi[3];
+  int ql[3], qh[3];
+};
+
+// grows the box to r cells around the cells [c0, c1], clipped to the grid of n cells a side
+__device__ __forceinline__ void box_grow(CellBox& b, const int c0[3], const int c1[3], int r,
+                                         int n) {
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    b.plo[a] = b.lo[a];
+    b.phi[a] = b.hi[a];
+    b.lo[a] = max(c0[a] - r, 0);
+    b.hi[a] = min(c1[a] + r, n - 1);
+  }
+}
+
+// Calls use(m, pq) with up to 64 probes at a time, pq in lanes 0 .. m - 1, for every probe in
+// a new cell of the box whose distance to the points is at most limit() (squared, lattice
+// units); limit() is read again for every 64 cells. Every lane of the wavefront calls it.
+template <typename Limit, typename Use>
+__device__ __forceinline__ void visit_new_cells(const ProbeGrid& g, const CellBox& b, int lane,
+                                                Limit limit, Use use) {
+  const int nx = b.hi[0] - b.lo[0] + 1, ny = b.hi[1] - b.lo[1] + 1;
+  const int ncell = nx * ny * (b.hi[2] - b.lo[2] + 1);
+  for (int base = 0; base < ncell; base += 64) {
+    const uint32_t most = limit();             // every lane takes part in it
+    const int i = base + lane;
+    const int row = i / nx;
+    const int c[3] = {b.lo[0] + i - row * nx, b.lo[1] + row % ny, b.lo[2] + row / ny};
+    bool inner = true;
+    uint32_t d2 = 0;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      inner = inner && c[a] >= b.plo[a] && c[a] <= b.phi[a];
+      const int c0 = c[a] << g.shift, c1 = c0 + (1 << g.shift) - 1;
+      const int d = max(max(c0 - b.qh[a], b.ql[a] - c1), 0);
+      d2 += (uint32_t)(d * d);
+    }
+    int e0 = 0, cnt = 0;
+    if (i < ncell && !inner && d2 <= most) {
+      const uint32_t m = morton3((uint32_t)c[0], (uint32_t)c[1], (uint32_t)c[2]);
+      e0 = g.cell_start[m];
+      cnt = g.cell_start[m + 1] - e0;
+    }
+    const int incl = wave_scan(cnt);
+    const int total = __builtin_amdgcn_readlane(incl, 63);
+    const int src = e0 - (incl - cnt);        // entry of candidate j of this lane's cell: src + j
+    for (int j0 = 0; j0 < total; j0 += 64) {
+      // the lane whose cell holds candidate j: the number of lanes with incl <= j
+      const int j = j0 + lane;
+      int own = 0;
+#pragma unroll
+      for (int s = 32; s > 0; s >>= 1)
+        if (__shfl(incl, own + s - 1) <= j) own += s;
+      const int e = __shfl(src, own & 63) + j;
+      const int m = min(total - j0, 64);
+      int4 pq = make_int4(0, 0, 0, 0);
+      if (lane < m) pq = g.qsorted[e];
+      use(m, pq);
+    }
+  }
+}
+
+// squared distance from lattice position q to the nearest cell outside the box (~0: none)
+__device__ __forceinline__ uint64_t outside_d2(const CellBox& b, const int q[3], int shift,
+                                               int n) {
+  uint64_t lb = ~0ull;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    if (b.lo[a] > 0) lb = min(lb, (uint64_t)(q[a] - (b.lo[a] << shift) + 1));
+    if (b.hi[a] < n - 1) lb = min(lb, (uint64_t)(((b.hi[a] + 1) << shift) - q[a]));
+  }
+  return lb == ~0ull ? lb : lb * lb;
+}
+
+// weight of a neighbour before the division by the sum (Eq. 10-11)
+__device__ __forceinline__ float knn_weight(const ProbeGrid& g, int p, v3 x, v3 n) {
+  const v3 d = sub(mk3(g.pos[3 * p], g.pos[3 * p + 1], g.pos[3 * p + 2]), x);
+  const float len = sqrtf(dot(d, d));
+  const float inv = 1.0f / len;
+  const float wb = 0.5f * (1.0f + dot(d, n) * inv) + 0.01f;
+  return inv * wb;
+}
+
+// One wavefront per point: the lanes test 64 probes at once and merge them into the point's
+// list by a sorting network. Bound by the latency of its few dependent loads until the points
+// fill the chip: 300 points among 64 probes take 10 us (a thread per point: 117 us), 4096
+// points 13 us (86).
+template <int K>
+__global__ __launch_bounds__(256) void k_knn_wave(ProbeGrid g, const float* pts,
+                                                  const float* normals, int64_t N,
+                                                  const int32_t* order, uint32_t lim,
+                                                  int32_t* out_idx, float* out_w) {
+  const int64_t t = (int64_t)blockIdx.x * 4 + wave_id_uniform();
+  if (t >= N) return;
+  const int lane = threadIdx.x & 63;
+  int64_t i = t;
+  if (order) {
+    const int32_t o = __builtin_amdgcn_readfirstlane(order[t]);
+    if ((uint64_t)o >= (uint64_t)N) return;
+    i = o;
+  }
+  const v3 x = mk3(pts[3 * i], pts[3 * i + 1], pts[3 * i + 2]);
+  const int G = 1 << g.bits;
+  int q[3] = {quantize1(x.x, g.lo[0], g.sc), quantize1(x.y, g.lo[1], g.sc),
+              quantize1(x.z, g.lo[2], g.sc)};
+  CellBox b;
+  int c[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    q[a] = __builtin_amdgcn_readfirstlane(q[a]);
+    c[a] = q[a] >> g.shift;
+    b.ql[a] = b.qh[a] = q[a];
+    b.lo[a] = 0;
+    b.hi[a] = -1;
+  }
+  uint64_t best = ~0ull;             // lane s of every row of 16: the s-th best key
+  uint32_t kth = ~0u;                // d^2 of the K-th best
+  for (int r = 1;; ++r) {
+    box_grow(b, c, c, r, G);
+    visit_new_cells(
+        g, b, lane, [&]() { return min(kth, lim); },
+        [&](int m, int4 pq) {
+          const int dx = pq.x - q[0], dy = pq.y - q[1], dz = pq.z - q[2];
+          const uint32_t d2 = (uint32_t)(dx * dx) + (uint32_t)(dy * dy) + (uint32_t)(dz * dz);
+          const bool in = lane < m && d2 <= min(kth, lim);
+          if (__ballot(in) == 0) return;
+          best = list_merge(best, in ? ((uint64_t)d2 << 32) | (uint32_t)pq.w : ~0ull, lane);
+          kth = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(best >> 32), K - 1);
+        });
+    const uint64_t lb2 = outside_d2(b, q, g.shift, G);
+    if (lb2 == ~0ull || lb2 > (uint64_t)lim) break;
+    // ~0 in the low half marks an empty entry (a probe index is below 2^31)
+    const uint32_t kid = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)best, K - 1);
+    if (kid != ~0u && (uint64_t)kth < lb2) break;
+  }
+  const bool found = (uint32_t)best != ~0u;
+  // exact hit: that probe alone
+  const bool hit = __builtin_amdgcn_readfirstlane((int)(uint32_t)best) != -1 &&
+                   __builtin_amdgcn_readfirstlane((int)(uint32_t)(best >> 32)) == 0;
+  const v3 n = mk3(normals[3 * i], normals[3 * i + 1], normals[3 * i + 2]);
+  const int p = (int)(uint32_t)best;
+  float wv = 0.0f;
+  if (lane < K && found) wv = knn_weight(g, p, x, n);
+  float sum = 0.0f;                  // added in list order
+#pragma unroll
+  for (int s = 0; s < K; ++s)
+    sum += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wv), s));
+  const float isum = 1.0f / sum;
+  if (lane < K) {
+    const bool keep = found && (!hit || lane == 0);
+    out_idx[i * K + lane] = keep ? p : -1;
+    out_w[i * K + lane] = keep ? (hit ? 1.0f : wv * isum) : 0.0f;
+  }
+}
+
 template <int K>
 __device__ __forceinline__ void insert_key(uint64_t (&best)[K], uint64_t key) {
   if (key < best[K - 1]) {
@@ -268,18 +525,26 @@ __device__ __forceinline__ void insert_key(uint64_t (&best)[K], uint64_t key) {
   }
 }
 
+// One lane per point, in processing order: the points of a wavefront lie in a few
+// neighbouring cells, so the wavefront searches for all its points within one cell of the
+// first unfinished one together, and every lane tests every probe of their box (the probe's
+// lattice position comes from a lane's register as a scalar). The points left over, across
+// a jump of the order, are taken in turn. Bound by the vector ALUs (the insertions): 200k
+// points among 4096 probes, K = 8, 52 us (a thread per point walking its own cells: 99 us),
+// 2.07M points among 16,384 probes 133 us (357).
 template <int K>
-__global__ __launch_bounds__(256) void k_knn(ProbeGrid g, const float* pts,
-                                             const float* normals, int64_t N,
-                                             const int32_t* order, uint32_t lim, int32_t* out_idx,
-                                             float* out_w) {
+__global__ __launch_bounds__(256) void k_knn_dense(ProbeGrid g, const float* pts,
+                                                   const float* normals, int64_t N,
+                                                   const int32_t* order, uint32_t lim,
+                                                   int32_t* out_idx, float* out_w) {
   const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (t >= N) return;
-  int64_t i = t;
-  if (order) {
+  const int lane = threadIdx.x & 63;
+  bool live = t < N;
+  int64_t i = live ? t : 0;
+  if (live && order) {
     const int32_t o = order[t];
-    if ((uint64_t)o >= (uint64_t)N) return;
-    i = o;
+    live = (uint64_t)o < (uint64_t)N;
+    i = live ? o : 0;
   }
   const v3 x = mk3(pts[3 * i], pts[3 * i + 1], pts[3 * i + 2]);
   const int q[3] = {quantize1(x.x, g.lo[0], g.sc), quantize1(x.y, g.lo[1], g.sc),
@@ -290,50 +555,47 @@ __global__ __launch_bounds__(256) void k_knn(ProbeGrid g, const float* pts,
 #pragma unroll
   for (int s = 0; s < K; ++s) best[s] = ~0ull;
 
-  auto visit = [&](int cx, int cy, int cz) {
-    const uint32_t m = morton3((uint32_t)cx, (uint32_t)cy, (uint32_t)cz);
-    const int32_t e0 = g.cell_start[m], e1 = g.cell_start[m + 1];
-    for (int32_t e = e0; e < e1; ++e) {
-      const int4 pq = g.qsorted[e];
-      const int dx = pq.x - q[0], dy = pq.y - q[1], dz = pq.z - q[2];
-      const uint32_t d2 = (uint32_t)(dx * dx) + (uint32_t)(dy * dy) + (uint32_t)(dz * dz);
-      if (d2 <= lim) insert_key<K>(best, ((uint64_t)d2 << 32) | (uint32_t)pq.w);
-    }
-  };
-
-  for (int r = 0;; ++r) {
-    // cells at Chebyshev distance exactly r from the point's cell
-    const int z0 = max(c[2] - r, 0), z1 = min(c[2] + r, G - 1);
-    const int y0 = max(c[1] - r, 0), y1 = min(c[1] + r, G - 1);
-    const int x0 = max(c[0] - r, 0), x1 = min(c[0] + r, G - 1);
-    for (int cz = z0; cz <= z1; ++cz) {
-      for (int cy = y0; cy <= y1; ++cy) {
-        if (abs(cz - c[2]) == r || abs(cy - c[1]) == r) {
-          for (int cx = x0; cx <= x1; ++cx) visit(cx, cy, cz);
-        } else {
-          if (c[0] - r >= 0) visit(c[0] - r, cy, cz);
-          if (c[0] + r <= G - 1) visit(c[0] + r, cy, cz);
-        }
-      }
-    }
-    // squared lattice distance to the nearest cell outside the visited cube
-    uint64_t lb = ~0ull;
+  uint64_t todo = __ballot(live);
+  while (todo != 0) {                              // uniform
+    const int first = __builtin_ctzll(todo);
+    bool act = ((todo >> lane) & 1) != 0;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) act = act && abs(c[a] - __builtin_amdgcn_readlane(c[a], first)) <= 1;
+    todo &= ~__ballot(act);
+    CellBox b;
+    int c0[3], c1[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-      if (c[a] - r > 0) {
-        const uint64_t d = (uint64_t)(q[a] - ((c[a] - r) << g.shift) + 1);
-        lb = d < lb ? d : lb;
-      }
-      if (c[a] + r + 1 <= G - 1) {
-        const uint64_t d = (uint64_t)((((c[a] + r + 1) << g.shift)) - q[a]);
-        lb = d < lb ? d : lb;
-      }
+      b.qh[a] = (int)wave_max_u32(act ? (uint32_t)q[a] : 0u);
+      b.ql[a] = 32767 - (int)wave_max_u32(act ? (uint32_t)(32767 - q[a]) : 0u);
+      c0[a] = b.ql[a] >> g.shift;
+      c1[a] = b.qh[a] >> g.shift;
+      b.lo[a] = 0;
+      b.hi[a] = -1;
     }
-    if (lb == ~0ull) break;                   // every cell visited
-    const uint64_t lb2 = lb * lb;
-    if (lb2 > (uint64_t)lim) break;           // nothing further is inside the radius
-    if (best[K - 1] != ~0ull && (best[K - 1] >> 32) < lb2) break;
+    for (int r = 1;; ++r) {
+      box_grow(b, c0, c1, r, G);
+      visit_new_cells(
+          g, b, lane,
+          [&]() { return min(wave_max_u32(act ? (uint32_t)(best[K - 1] >> 32) : 0u), lim); },
+          [&](int m, int4 pq) {
+            for (int j = 0; j < m; ++j) {
+              const int dx = __builtin_amdgcn_readlane(pq.x, j) - q[0];
+              const int dy = __builtin_amdgcn_readlane(pq.y, j) - q[1];
+              const int dz = __builtin_amdgcn_readlane(pq.z, j) - q[2];
+              const uint32_t id = (uint32_t)__builtin_amdgcn_readlane(pq.w, j);
+              const uint32_t d2 =
+                  (uint32_t)(dx * dx) + (uint32_t)(dy * dy) + (uint32_t)(dz * dz);
+              if (act && d2 <= lim) insert_key<K>(best, ((uint64_t)d2 << 32) | id);
+            }
+          });
+      const uint64_t lb2 = outside_d2(b, q, g.shift, G);
+      const bool more = act && lb2 != ~0ull && lb2 <= (uint64_t)lim &&
+                        !(best[K - 1] != ~0ull && (best[K - 1] >> 32) < lb2);
+      if (__ballot(more) == 0) break;
+    }
   }
+  if (!live) return;
 
   int32_t* oi = out_idx + i * K;
   float* ow = out_w + i * K;
@@ -352,16 +614,8 @@ __global__ __launch_bounds__(256) void k_knn(ProbeGrid g, const float* pts,
   float sum = 0.0f;
 #pragma unroll
   for (int s = 0; s < K; ++s) {
-    wv[s] = 0.0f;
-    if (best[s] != ~0ull) {
-      const int p = (int)(best[s] & 0xFFFFFFFFu);
-      const v3 d = sub(mk3(g.pos[3 * p], g.pos[3 * p + 1], g.pos[3 * p + 2]), x);
-      const float len = sqrtf(dot(d, d));
-      const float inv = 1.0f / len;
-      const float wb = 0.5f * (1.0f + dot(d, n) * inv) + 0.01f;
-      wv[s] = inv * wb;
-      sum += wv[s];
-    }
+    wv[s] = best[s] != ~0ull ? knn_weight(g, (int)(best[s] & 0xFFFFFFFFu), x, n) : 0.0f;
+    sum += wv[s];
   }
   const float isum = 1.0f / sum;
 #pragma unroll
@@ -372,12 +626,21 @@ __global__ __launch_bounds__(256) void k_knn(ProbeGrid g, const float* pts,
   }
 }
 
+constexpr int64_t kKnnWavePoints = 16384;
+static bool knn_by_wave(const ProbeGrid& g, int64_t N) {
+  return N <= kKnnWavePoints || N < 4 * (int64_t)g.P;
+}
+
 template <int K>
 static hipError_t knn_k(const ProbeGrid& g, const float* pts, const float* normals, int64_t N,
                         const int32_t* order, uint32_t lim, int32_t* idx, float* w,
                         hipStream_t s) {
-  hipLaunchKernelGGL(k_knn<K>, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, s, g, pts,
-                     normals, N, order, lim, idx, w);
+  if (knn_by_wave(g, N))
+    hipLaunchKernelGGL(k_knn_wave<K>, dim3((unsigned)((N + 3) / 4)), dim3(256), 0, s, g, pts,
+                       normals, N, order, lim, idx, w);
+  else
+    hipLaunchKernelGGL(k_knn_dense<K>, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, s, g,
+                       pts, normals, N, order, lim, idx, w);
   return hipGetLastError();
 }
 

@@ -1,0 +1,68 @@
+"""Neighbour search: both kernels (a wavefront per point for small calls, a lane per point for
+large ones) find exactly the oracle's probes, at the sizes where their grids, lists and boxes
+change, and agree bit for bit with each other."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+LO, HI = np.full(3, -1.05, np.float32), np.full(3, 1.05, np.float32)
+
+
+def cloud(kind, n, g):
+    v = g.standard_normal((n, 3))
+    v /= np.linalg.norm(v, axis=1, keepdims=True)
+    if kind == "corner":                       # everything in one grid cell of the box
+        v = -1.0 + 0.01 * g.random((n, 3))
+    elif kind == "outside":                    # beyond the box on every side (clamped)
+        v *= 1.7
+    elif kind == "same":                       # equal distances: ties go to the lower index
+        v = np.repeat(v[: (n + 3) // 4], 4, axis=0)[:n]
+    return v.astype(np.float32)
+
+
+@pytest.mark.parametrize("P,N,K,probes,points,radius", [
+    (1, 5, 1, "sphere", "sphere", np.inf),
+    (3, 70, 4, "sphere", "sphere", np.inf),          # fewer probes than entries
+    (64, 301, 4, "sphere", "sphere", np.inf),
+    (65, 20_000, 16, "sphere", "sphere", np.inf),    # 16-entry lists, a lane per point
+    (1000, 4097, 9, "same", "sphere", np.inf),
+    (1000, 16_384, 8, "corner", "sphere", np.inf),   # boxes grow over the whole grid
+    (1000, 16_385, 8, "corner", "sphere", np.inf),
+    (4096, 16_500, 8, "sphere", "outside", np.inf),
+    (4096, 17_000, 5, "outside", "sphere", 0.2),     # radius-limited lists with gaps
+    (300, 40_003, 8, "same", "same", np.inf),        # points on probes: exact hits
+    (300, 2_003, 3, "sphere", "corner", 0.05),       # nothing within the radius
+])
+def test_search_exact(P, N, K, probes, points, radius):
+    import torch
+
+    from paper_2510_07729_amd import sop
+    g = np.random.default_rng(P * 31 + N)
+    pp, x = cloud(probes, P, g), cloud(points, N, g)
+    if probes == points == "same":
+        x[: P] = pp
+    nrm = cloud("sphere", N, g)
+    dev = lambda a: torch.from_numpy(a).cuda()
+    plan = sop.Plan(dev(pp), LO, HI)
+    zero = torch.zeros(1, device="cuda")
+    knn = lambda a, b: sop.sop_knn(plan, sop.Points(dev(x[a:b]), dev(nrm[a:b]), zero, zero, zero),
+                                   K, radius)
+    nb = knn(0, N)
+    assert np.array_equal(np.sort(nb.order.cpu().numpy()), np.arange(N))
+    idx, w = nb.idx.cpu().numpy(), nb.w.cpu().numpy()
+    rows = g.choice(N, min(N, 3000), replace=False)
+    ridx, rw = oracle.knn(pp, LO, HI, x[rows], nrm[rows], K, radius)
+    assert np.array_equal(idx[rows], ridx)
+    # a weight is a quotient of sums of K terms of a few float32 roundings each; |p - x| comes
+    # from rounded differences, exact to 2^-24 of the coordinates
+    gap = np.sqrt(((pp[np.maximum(ridx, 0)] - x[rows][:, None].astype(np.float64)) ** 2).sum(-1))
+    gap = np.where(ridx < 0, np.inf, gap).min(1, keepdims=True)
+    tol = 2.0 ** -24 * (32 + 8 / np.maximum(gap, 1e-7))
+    assert np.all(np.abs(w[rows] - rw) <= tol)
+    for a in range(0, min(N, 48_000), 12_000):      # the same points in small calls
+        part = knn(a, min(N, a + 12_000))
+        assert torch.equal(part.idx, nb.idx[a:a + 12_000])
+        assert torch.equal(part.w, nb.w[a:a + 12_000])
