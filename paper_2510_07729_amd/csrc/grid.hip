@@ -167,61 +167,112 @@ hipError_t launch_probe_grid_build(const float* pos, int32_t P, const float lo[3
 // ------------------------------------------------------------------------------------------
 // point ordering: counting sort by Morton cell
 // ------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_point_cells(ProbeGrid g, const float* pts, int64_t N,
-                                                     int32_t* point_cell, int32_t* counts) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= N) return;
-  const int qx = quantize1(pts[3 * i], g.lo[0], g.sc);
-  const int qy = quantize1(pts[3 * i + 1], g.lo[1], g.sc);
-  const int qz = quantize1(pts[3 * i + 2], g.lo[2], g.sc);
-  const uint32_t m = cell_of(qx, qy, qz, g.shift);
-  point_cell[i] = (int32_t)m;
-  atomicAdd(&counts[m], 1);
+__device__ __forceinline__ uint32_t point_cell(const ProbeGrid& g, const float* pts, int64_t i) {
+  return cell_of(quantize1(pts[3 * i], g.lo[0], g.sc), quantize1(pts[3 * i + 1], g.lo[1], g.sc),
+                 quantize1(pts[3 * i + 2], g.lo[2], g.sc), g.shift);
 }
 
-__global__ __launch_bounds__(256) void k_point_scatter(const int32_t* point_cell, int64_t N,
-                                                       int32_t* offsets, int32_t* order) {
+// Counts the points of every cell and keeps each point's rank in its cell, so that the
+// scatter needs no atomics of its own. An atomic costs its request at memory, ~10 G/s, so
+// there is one per run of lanes in the same cell (neighbouring pixels mostly are: a
+// 1920x1080 frame takes 21 us and its scatter 8, against 562 and 822 us with one atomic per
+// point in each) ...
+__global__ __launch_bounds__(256) void k_point_rank(ProbeGrid g, const float* pts, int64_t N,
+                                                    int32_t* counts, int32_t* rank) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int lane = threadIdx.x & 63;
+  const int32_t m = i < N ? (int32_t)point_cell(g, pts, i) : -1;
+  const int32_t before = __shfl_up(m, 1);
+  const bool head = lane == 0 || before != m;
+  const uint64_t heads = __ballot(head);
+  const uint64_t upto = heads & (~0ull >> (63 - lane));       // heads at or below the lane
+  const int first = 63 - __builtin_clzll(upto);
+  int32_t base = 0;
+  if (head && m >= 0) {
+    const uint64_t after = lane == 63 ? 0 : heads >> (lane + 1);
+    const int len = after ? __builtin_ctzll(after) + 1 : 64 - lane;
+    base = atomicAdd(&counts[m], len);
+  }
+  base = __shfl(base, first);
+  if (i < N) rank[i] = base + lane - first;
+}
+
+// ... and, for grids of up to kTableCells cells, one per cell and chunk of kTablePoints
+// points, counted in LDS first (points in no order: 500k over 900 cells 22 + 7 us, against 70
+// + 96). Calls of one chunk have nothing to gain from the table.
+constexpr int kTableCells = 32768;
+constexpr int kTablePer = 4;
+constexpr int kTablePoints = 1024 * kTablePer;
+__global__ __launch_bounds__(1024) void k_point_rank_table(ProbeGrid g, const float* pts,
+                                                           int64_t N, int32_t* counts,
+                                                           int32_t* rank) {
+  extern __shared__ int32_t cnt[];                            // [cells], a multiple of 4
+  const int cells = 1 << (3 * g.bits), tid = threadIdx.x;
+  for (int c = 4 * tid; c < cells; c += 4096)
+    *reinterpret_cast<int4*>(cnt + c) = make_int4(0, 0, 0, 0);
+  __syncthreads();
+  int32_t m[kTablePer], r[kTablePer];
+#pragma unroll
+  for (int u = 0; u < kTablePer; ++u) {
+    const int64_t i = (int64_t)blockIdx.x * kTablePoints + u * 1024 + tid;
+    m[u] = i < N ? (int32_t)point_cell(g, pts, i) : -1;
+    r[u] = m[u] >= 0 ? atomicAdd(&cnt[m[u]], 1) : -1;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kTablePer; ++u)
+    if (r[u] == 0) cnt[m[u]] = atomicAdd(&counts[m[u]], cnt[m[u]]);   // the chunk's first rank
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kTablePer; ++u) {
+    const int64_t i = (int64_t)blockIdx.x * kTablePoints + u * 1024 + tid;
+    if (i < N) rank[i] = cnt[m[u]] + r[u];
+  }
+}
+
+__global__ __launch_bounds__(256) void k_point_scatter(ProbeGrid g, const float* pts, int64_t N,
+                                                       const int32_t* start,
+                                                       const int32_t* rank, int32_t* out) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= N) return;
-  const int32_t slot = atomicAdd(&offsets[point_cell[i]], 1);
-  order[slot] = (int32_t)i;
+  out[start[point_cell(g, pts, i)] + rank[i]] = (int32_t)i;
 }
 
 // Orders the points of each grid cell by the Morton code of their lattice position inside
 // the cell (10 bits per axis), ties by point index: consecutive points of the order then
 // lie close together at the scale of a few points, not only of a cell, so a batch of them
 // shares more neighbouring probes (the adjoint adds each batch's texture gradient once per
-// distinct probe). One workgroup per cell, bitonic sort in LDS; a cell of more than
-// kRefineMax points keeps the counting sort's order. Also makes the order deterministic.
+// distinct probe). A cell of more than kRefineMax points keeps the counting sort's order.
+// Also makes the order deterministic. Most cells of a grid are empty, so a workgroup looks at
+// up to 64 of them, spread over the grid. It places each point of a cell by counting the
+// smaller keys: of the whole cell up to 256 points, and above that of its bin, the top 12
+// bits of the code (a bitonic sort of every cell is bound by its LDS passes: 99 us on 500k
+// points in 900 cells, 35 us this way); a cell with a bin of more than kBinMax
+// points, whose counts would grow with the square of it, is still sorted.
 constexpr int kRefineMax = 4096;
-__global__ __launch_bounds__(256) void k_point_refine(ProbeGrid g, const float* pts,
-                                                      const int32_t* ends, int32_t* order) {
-  __shared__ uint64_t key[kRefineMax];
-  const int32_t c = blockIdx.x;
-  const int32_t s0 = c == 0 ? 0 : ends[c - 1], s1 = ends[c];
-  const int n = s1 - s0;
-  if (n <= 1 || n > kRefineMax) return;
+constexpr int kRefineBlocks = 4096;
+constexpr int kBins = 4096;
+constexpr int kBinMax = 128;
+constexpr int kRefinePer = kRefineMax / 256;
+
+// the number of keys below k among key[a, b)
+template <int UNROLL>
+__device__ __forceinline__ int count_below(const uint64_t* key, int a, int b, uint64_t k) {
+  int c = 0;
+#pragma unroll UNROLL
+  for (int j = a; j < b; ++j) c += key[j] < k ? 1 : 0;
+  return c;
+}
+
+__device__ __forceinline__ void bitonic_sort(uint64_t* key, int n) {
   int m = 1;
   while (m < n) m <<= 1;
-  const int fine = g.shift < 10 ? g.shift : 10;           // bits per axis inside the cell
-  const uint32_t mask = (1u << g.shift) - 1u;
-  for (int i = threadIdx.x; i < m; i += 256) {
-    uint64_t kv = ~0ull;
-    if (i < n) {
-      const int32_t p = order[s0 + i];
-      const uint32_t qx = (uint32_t)quantize1(pts[3 * (int64_t)p], g.lo[0], g.sc) & mask;
-      const uint32_t qy = (uint32_t)quantize1(pts[3 * (int64_t)p + 1], g.lo[1], g.sc) & mask;
-      const uint32_t qz = (uint32_t)quantize1(pts[3 * (int64_t)p + 2], g.lo[2], g.sc) & mask;
-      const int sh = g.shift - fine;
-      kv = ((uint64_t)morton3(qx >> sh, qy >> sh, qz >> sh) << 32) | (uint32_t)p;
-    }
-    key[i] = kv;
-  }
+  for (int i = n + (int)threadIdx.x; i < m; i += 256) key[i] = ~0ull;
   __syncthreads();
   for (int size = 2; size <= m; size <<= 1)
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
+    for (int step = size >> 1; step > 0; step >>= 1) {
       for (int t = threadIdx.x; t < m / 2; t += 256) {
-        const int i = 2 * stride * (t / stride) + (t % stride), j = i + stride;
+        const int i = 2 * t - (t & (step - 1)), j = i + step;
         const uint64_t x = key[i], y = key[j];
         if ((x > y) == ((i & size) == 0)) {
           key[i] = y;
@@ -230,26 +281,123 @@ __global__ __launch_bounds__(256) void k_point_refine(ProbeGrid g, const float* 
       }
       __syncthreads();
     }
-  for (int i = threadIdx.x; i < n; i += 256) order[s0 + i] = (int32_t)(key[i] & 0xFFFFFFFFu);
+}
+
+__global__ __launch_bounds__(256) void k_point_refine(ProbeGrid g, const float* pts,
+                                                      const int32_t* start, int32_t cells,
+                                                      const int32_t* in, int32_t* order) {
+  __shared__ uint64_t key[kRefineMax];
+  __shared__ int32_t bin[kBins + 1];                      // count, then first place of each bin
+  __shared__ int32_t sums[kScanThreads];
+  const int tid = threadIdx.x;
+  const int32_t stride = (int32_t)gridDim.x;
+  const int fine = g.shift < 10 ? g.shift : 10;           // bits per axis inside the cell
+  const int sh = g.shift - fine, bsh = 32 + (fine > 4 ? 3 * fine - 12 : 0);
+  const uint32_t mask = (1u << g.shift) - 1u;
+  auto key_of = [&](int32_t p) {
+    const uint32_t qx = (uint32_t)quantize1(pts[3 * (int64_t)p], g.lo[0], g.sc) & mask;
+    const uint32_t qy = (uint32_t)quantize1(pts[3 * (int64_t)p + 1], g.lo[1], g.sc) & mask;
+    const uint32_t qz = (uint32_t)quantize1(pts[3 * (int64_t)p + 2], g.lo[2], g.sc) & mask;
+    return ((uint64_t)morton3(qx >> sh, qy >> sh, qz >> sh) << 32) | (uint32_t)p;
+  };
+  for (int32_t c0 = blockIdx.x; c0 < cells; c0 += 64 * stride) {
+    const int64_t mine = (int64_t)c0 + (int64_t)(tid & 63) * stride;
+    int32_t b0 = 0, bn = 0;
+    if (mine < cells) {
+      b0 = start[mine];
+      bn = start[mine + 1] - b0;
+    }
+    for (uint64_t some = __ballot(bn > 0); some != 0; some &= some - 1) {   // uniform
+      const int l = __builtin_ctzll(some);
+      const int32_t s0 = __builtin_amdgcn_readlane(b0, l), n = __builtin_amdgcn_readlane(bn, l);
+      if (n == 1 || n > kRefineMax) {
+        for (int i = tid; i < n; i += 256) order[s0 + i] = in[s0 + i];
+        continue;
+      }
+      __syncthreads();                                     // the cell before is done
+      if (n <= 256) {
+        uint64_t k = 0;
+        if (tid < n) key[tid] = k = key_of(in[s0 + tid]);
+        __syncthreads();
+        if (tid < n) order[s0 + count_below<8>(key, 0, n, k)] = (int32_t)(uint32_t)k;
+        continue;
+      }
+      for (int i = tid; i < kBins / 4; i += 256)
+        reinterpret_cast<int4*>(bin)[i] = make_int4(0, 0, 0, 0);
+      __syncthreads();
+      uint64_t k[kRefinePer];
+      int32_t r[kRefinePer];
+#pragma unroll
+      for (int u = 0; u < kRefinePer; ++u) {
+        const int i = tid + 256 * u;
+        if (i < n) {
+          k[u] = key_of(in[s0 + i]);
+          r[u] = atomicAdd(&bin[(int)(k[u] >> bsh)], 1);
+        }
+      }
+      __syncthreads();
+      int32_t cnt[kBins / 256], own = 0;
+      bool large = false;
+#pragma unroll
+      for (int u = 0; u < kBins / 256; ++u) {
+        cnt[u] = bin[tid * (kBins / 256) + u];
+        own += cnt[u];
+        large = large || cnt[u] > kBinMax;
+      }
+      int32_t total;
+      int32_t at = block_exclusive(own, sums, &total);
+#pragma unroll
+      for (int u = 0; u < kBins / 256; ++u) {
+        bin[tid * (kBins / 256) + u] = at;
+        at += cnt[u];
+      }
+      if (tid == 255) bin[kBins] = n;
+      const bool sort = __syncthreads_or(large) != 0;
+#pragma unroll
+      for (int u = 0; u < kRefinePer; ++u)
+        if (tid + 256 * u < n) key[bin[(int)(k[u] >> bsh)] + r[u]] = k[u];
+      __syncthreads();
+      if (sort) {
+        bitonic_sort(key, n);
+        for (int i = tid; i < n; i += 256) order[s0 + i] = (int32_t)(uint32_t)key[i];
+        continue;
+      }
+#pragma unroll
+      for (int u = 0; u < kRefinePer; ++u)
+        if (tid + 256 * u < n) {
+          const int q = (int)(k[u] >> bsh), first = bin[q];
+          order[s0 + first + count_below<1>(key, first, bin[q + 1], k[u])] =
+              (int32_t)(uint32_t)k[u];
+        }
+    }
+  }
 }
 
 hipError_t launch_point_order(const ProbeGrid& g, const float* pts, int64_t N,
-                              int32_t* point_cell, int32_t* counts, int32_t* offsets,
+                              int32_t* by_cell, int32_t* counts, int32_t* offsets,
                               int32_t* scan_tmp, int32_t* order, hipStream_t s) {
   if (N == 0) return hipSuccess;
   const size_t C = (size_t)1 << (3 * g.bits);
   hipError_t e = launch_fill_i32(counts, 0, C, s);
   if (e != hipSuccess) return e;
   const unsigned blocks = (unsigned)((N + 255) / 256);
-  hipLaunchKernelGGL(k_point_cells, dim3(blocks), dim3(256), 0, s, g, pts, N, point_cell,
-                     counts);
+  int32_t* rank = order;                       // until the order itself is written
+  if (C <= (size_t)kTableCells && N > kTablePoints) {
+    const size_t lds = C * sizeof(int32_t);
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_point_rank_table),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL(k_point_rank_table, dim3((unsigned)((N + kTablePoints - 1) / kTablePoints)),
+                       dim3(1024), lds, s, g, pts, N, counts, rank);
+  } else {
+    hipLaunchKernelGGL(k_point_rank, dim3(blocks), dim3(256), 0, s, g, pts, N, counts, rank);
+  }
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if ((e = launch_exclusive_scan(counts, offsets, C, scan_tmp, s)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_point_scatter, dim3(blocks), dim3(256), 0, s, point_cell, N, offsets,
-                     order);
+  hipLaunchKernelGGL(k_point_scatter, dim3(blocks), dim3(256), 0, s, g, pts, N, offsets, rank,
+                     by_cell);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  // after the scatter offsets[c] holds the end of cell c
-  hipLaunchKernelGGL(k_point_refine, dim3((unsigned)C), dim3(256), 0, s, g, pts, offsets, order);
+  hipLaunchKernelGGL(k_point_refine, dim3((unsigned)std::min<size_t>(C, kRefineBlocks)), dim3(256),
+                     0, s, g, pts, offsets, (int32_t)C, by_cell, order);
   return hipGetLastError();
 }
 
@@ -626,10 +774,12 @@ __global__ __launch_bounds__(256) void k_knn_dense(ProbeGrid g, const float* pts
   }
 }
 
-constexpr int64_t kKnnWavePoints = 16384;
-static bool knn_by_wave(const ProbeGrid& g, int64_t N) {
-  return N <= kKnnWavePoints || N < 4 * (int64_t)g.P;
-}
+// The lines cross where a wavefront's 64 consecutive points begin to share cells. Whole
+// sop_knn calls at K = 8, wavefront / lane per point: 64 probes (8 cells a side) 8192 points
+// 45 / 53 us, 16,384 points 57 / 52; 512 probes (16) 16,384 points 55 / 67, 32,768 points
+// 76 / 65; 4096 probes (32) 32,768 points 78 / 99, 65,536 points 113 / 99; 16,384 probes (64)
+// 65,536 points 129 / 140, 131,072 points 213 / 159.
+static bool knn_by_wave(const ProbeGrid& g, int64_t N) { return N <= (int64_t)1536 << g.bits; }
 
 template <int K>
 static hipError_t knn_k(const ProbeGrid& g, const float* pts, const float* normals, int64_t N,

@@ -47,7 +47,7 @@ hipError_t launch_probe_grid_build(const float* pos, int32_t P, const float lo[3
                                    float* pos_copy, int32_t* scan_tmp, hipStream_t s);
 // points -> processing order grouped by grid cell (counting sort by Morton cell)
 hipError_t launch_point_order(const ProbeGrid& g, const float* pts, int64_t N,
-                              int32_t* point_cell, int32_t* counts, int32_t* offsets,
+                              int32_t* by_cell, int32_t* counts, int32_t* offsets,
                               int32_t* scan_tmp, int32_t* order, hipStream_t s);
 hipError_t launch_knn(const ProbeGrid& g, const float* pts, const float* normals, int64_t N,
                       const int32_t* order, int32_t k, uint32_t radius_limit, int32_t* idx,

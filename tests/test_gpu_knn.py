@@ -66,3 +66,46 @@ def test_search_exact(P, N, K, probes, points, radius):
         part = knn(a, min(N, a + 12_000))
         assert torch.equal(part.idx, nb.idx[a:a + 12_000])
         assert torch.equal(part.w, nb.w[a:a + 12_000])
+
+
+def spread(v):
+    return sum(((v >> b) & 1) << (3 * b) for b in range(10))
+
+
+@pytest.mark.parametrize("P,N,side", [
+    (64, 300, 2.0), (64, 4097, 2.0),           # runs of lanes; 8 cells a side
+    (64, 20_000, 0.3),                         # cells of ~2000 points: bins
+    (64, 40_000, 0.2),                         # cells beyond the sorted size stay whole
+    (4096, 60_000, 2.0), (16_384, 60_000, 2.0),
+    (64, 5000, 0.0), (4096, 3000, 1e-4),       # one place: a bin above the counted size
+    (64, 4096, 0.25), (64, 257, 0.1), (64, 256, 0.1),
+])
+def test_processing_order(P, N, side):
+    import torch
+
+    from paper_2510_07729_amd import sop
+    g = np.random.default_rng(N + P)
+    x = (side * (g.random((N, 3)) - 0.5)).astype(np.float32) + np.float32(0.011)
+    if N == 300:
+        x = x[np.argsort(x[:, 0])]
+    plan = sop.Plan(torch.from_numpy(cloud("sphere", P, g)).cuda(), LO, HI)
+    z = torch.zeros(1, device="cuda")
+    pts = torch.from_numpy(x).cuda()
+    run = lambda: sop.sop_knn(plan, sop.Points(pts, pts, z, z, z), 1).order.cpu().numpy()
+    order = run()
+    assert np.array_equal(np.sort(order), np.arange(N))
+    _, dims, sc = plan.info()
+    bits = int(np.log2(dims[0]))
+    q = np.floor((x - LO) * np.float32(sc)).astype(np.int64)
+    shift = 15 - bits
+    cell = sum(spread(q[:, a] >> shift) << a for a in range(3))
+    fine = min(shift, 10)
+    code = sum(spread((q[:, a] & ((1 << shift) - 1)) >> (shift - fine)) << a for a in range(3))
+    c = cell[order]
+    assert np.all(np.diff(c) >= 0)
+    n_in = np.bincount(cell, minlength=c.max() + 1)
+    want = np.lexsort((np.arange(N), code, cell))
+    small = n_in[c] <= 4096
+    assert np.array_equal(order[small], want[small])
+    if small.all():
+        assert np.array_equal(order, run())
