@@ -92,13 +92,14 @@ struct FpsArgs {
   int32_t* chosen;   // [P]
 };
 
-// Thread t of workgroup b owns the points j = b * 256 + t + u * (256 * gridDim.x). Pick k
+// Larger clouds, streamed from pd: one exchange per pick (a pick reads the whole cloud, which
+// takes longer than the exchange). Thread t of workgroup b owns the points
+// j = b * 256 + t + u * (256 * gridDim.x). Pick k
 // (1 <= k < P): the pick of step k-1 lowers every point's distance; the workgroup maximum
 // goes into row k % 3 with tag k & 3; the pick is the maximum of that row once every word
 // carries the tag. A word of row k % 3 still holds pick k - 3 (tag (k + 1) & 3) or the zero
 // of the launch until its workgroup writes pick k, and no workgroup can write pick k + 3
 // before every workgroup has read pick k + 1, so a wait never sees a later pick.
-template <int U>   // U > 0: U points per thread in registers; U == 0: points in pd
 __global__ __launch_bounds__(256) void k_fps(FpsArgs a) {
   __shared__ uint64_t s_part[4], s_win;
   __shared__ float s_xyz[3];
@@ -106,39 +107,18 @@ __global__ __launch_bounds__(256) void k_fps(FpsArgs a) {
   const int t = threadIdx.x, w = t >> 6;
   const int G = (int)gridDim.x;
   const int64_t T = (int64_t)G * 256, j0 = (int64_t)blockIdx.x * 256 + t;
-  float4 p[U > 0 ? U : 1];
-  if constexpr (U > 0) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t j = j0 + u * T;
-      p[u] = j < a.M ? make_float4(a.pts[3 * j], a.pts[3 * j + 1], a.pts[3 * j + 2],
-                                   __int_as_float(0x7F800000))
-                     : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-  }
   int64_t q = a.start;
   float cx = a.pts[3 * q], cy = a.pts[3 * q + 1], cz = a.pts[3 * q + 2];
   for (int32_t k = 1; k < a.P; ++k) {
     if (blockIdx.x == 0 && t == 0) a.chosen[k - 1] = (int32_t)q;
     const float4 c = make_float4(cx, cy, cz, 0.f);
     uint64_t best = 0;
-    if constexpr (U > 0) {
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int64_t j = j0 + u * T;
-        if (j < a.M) {
-          p[u].w = fminf(p[u].w, fps_d2(p[u], c));
-          best = max_u64(best, fps_key(p[u].w, j));
-        }
-      }
-    } else {
-      for (int64_t j = j0; j < a.M; j += T) {
-        const float4 x = a.pd[j];
-        const float d2 = fps_d2(x, c);
-        // only a distance that shrinks is written back (after the first picks most do not)
-        if (d2 < x.w) reinterpret_cast<float*>(a.pd + j)[3] = d2;
-        best = max_u64(best, fps_key(fminf(x.w, d2), j));
-      }
+    for (int64_t j = j0; j < a.M; j += T) {
+      const float4 x = a.pd[j];
+      const float d2 = fps_d2(x, c);
+      // only a distance that shrinks is written back (after the first picks most do not)
+      if (d2 < x.w) reinterpret_cast<float*>(a.pd + j)[3] = d2;
+      best = max_u64(best, fps_key(fminf(x.w, d2), j));
     }
     for (int o = 32; o > 0; o >>= 1) best = max_u64(best, shfl_xor_u64(best, o));
     if ((t & 63) == 0) s_part[w] = best;
@@ -203,6 +183,259 @@ __global__ __launch_bounds__(256) void k_fps(FpsArgs a) {
   if (blockIdx.x == 0 && t == 0) a.chosen[a.P - 1] = (int32_t)q;
 }
 
+// Clouds that fit in registers (up to 64 workgroups x 256 threads x 32 points): picks in
+// rounds. A pick costs little; exchanging it between the workgroups costs a round trip
+// through memory (3.0 us), so a round exchanges many. Every wavefront publishes its T points
+// of largest key and the largest key it holds back; B is the largest key held back anywhere.
+// A distance only ever shrinks, so as long as the best of the published points has a key
+// above B it is the next pick, exactly: each workgroup takes these picks for itself, lowering
+// the published points' distances, until the best falls to B, and then lowers its own points
+// by all the round's picks at once. The first pick of a round is always above B. On the
+// object's 65,536 samples a round takes 60 picks: 4096 picks in FPS_NOW us against 12,200 us
+// with an exchange per pick; what is left is the serial chain of a pick (a reduction over
+// one wavefront) and ~70 exchanges.
+//
+// Round r uses row r % 3 of published words with tag r & 3, as the picks of k_fps do: a word
+// of the row still holds round r - 3 or the zero of the launch until its wavefront writes
+// round r, and no wavefront writes round r + 3 before every workgroup has read round r + 1.
+constexpr int kFpsCand = 1024;   // most published points of a round
+struct FpsRoundArgs {
+  const float* pts;  // [M,3]
+  int64_t M;
+  int32_t P;
+  int64_t start;
+  uint64_t* rows;    // [3][gridDim.x * 4 * (T + 1)] published words, zero at launch
+  int32_t* fault;    // set when a wait gave up, zero at launch
+  int32_t* chosen;   // [P]
+};
+
+__device__ __forceinline__ uint32_t fps_wave_max(uint32_t v) {
+#define SOP_FPS_STEP(CTRL, ROWS) \
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, ROWS, 0xF, false))
+  SOP_FPS_STEP(0xB1, 0xF);     // quad_perm [1,0,3,2]
+  SOP_FPS_STEP(0x4E, 0xF);     // quad_perm [2,3,0,1]
+  SOP_FPS_STEP(0x141, 0xF);    // row_half_mirror
+  SOP_FPS_STEP(0x140, 0xF);    // row_mirror
+  SOP_FPS_STEP(0x142, 0xA);    // row_bcast15 into rows 1, 3
+  SOP_FPS_STEP(0x143, 0xC);    // row_bcast31 into rows 2, 3
+#undef SOP_FPS_STEP
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// the largest key of the wavefront (distances first, then the inverted indices of the lanes
+// that hold the largest distance)
+__device__ __forceinline__ uint64_t fps_wave_max_key(uint64_t k) {
+  const uint32_t hi = fps_wave_max((uint32_t)(k >> 32));
+  const bool top = (uint32_t)(k >> 32) == hi;
+  return ((uint64_t)hi << 32) | fps_wave_max(top ? (uint32_t)k : 0u);
+}
+
+// The picks of one round over n candidates in LDS (pos, and low word of the key; key in
+// s_key), R per lane of one wavefront: up to `most` picks into s_pick and s_pid.
+template <int R>
+__device__ __forceinline__ int fps_round_picks(int n, uint64_t bound, int most, int lane,
+                                               const float4* s_pos, const uint64_t* s_key,
+                                               float4* s_pick, int32_t* s_pid) {
+  float4 p[R];
+  uint32_t inv[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int c = r * 64 + lane;
+    p[r] = make_float4(0.f, 0.f, 0.f, 0.f);
+    inv[r] = 0;                                   // no candidate: never the largest key
+    if (c < n) {
+      p[r] = s_pos[c];
+      p[r].w = __uint_as_float((uint32_t)(s_key[c] >> 32));
+      inv[r] = (uint32_t)s_key[c];
+    }
+  }
+  int np = 0;
+  while (np < most) {
+    uint32_t d = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) d = max(d, __float_as_uint(p[r].w));
+    const uint32_t top = fps_wave_max(d);
+    uint32_t q = 0;                                // largest inverted index at that distance
+#pragma unroll
+    for (int r = 0; r < R; ++r) q = max(q, __float_as_uint(p[r].w) == top ? inv[r] : 0u);
+    const uint64_t have = __ballot(q != 0);
+    uint32_t win;
+    if ((have & (have - 1)) == 0)
+      win = (uint32_t)__builtin_amdgcn_readlane((int)q, __builtin_ctzll(have | (1ull << 63)));
+    else
+      win = fps_wave_max(q);                       // equal distances: the lowest index
+    if ((((uint64_t)top << 32) | win) <= bound) break;
+    float x = 0.f, y = 0.f, z = 0.f;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (inv[r] == win) {
+        x = p[r].x;
+        y = p[r].y;
+        z = p[r].z;
+      }
+    const int l = __builtin_ctzll(__ballot(q == win) | (1ull << 63));
+    const float4 c = make_float4(
+        __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l)),
+        __int_as_float(__builtin_amdgcn_readlane(__float_as_int(y), l)),
+        __int_as_float(__builtin_amdgcn_readlane(__float_as_int(z), l)), 0.f);
+#pragma unroll
+    for (int r = 0; r < R; ++r) p[r].w = fminf(p[r].w, fps_d2(p[r], c));
+    if (lane == 0) {
+      s_pick[np] = c;
+      s_pid[np] = (int32_t)(0xFFFFFFFFu - win);
+    }
+    ++np;
+  }
+  return np;
+}
+
+template <int U, int T>   // U points per thread, T published points per wavefront
+__global__ __launch_bounds__(256) void k_fps_rounds(FpsRoundArgs a) {
+  __shared__ float4 s_pos[kFpsCand], s_pick[kFpsCand];
+  __shared__ uint64_t s_key[kFpsCand], s_bound[4];
+  __shared__ int32_t s_pid[kFpsCand], s_n, s_np, s_late;
+  constexpr int W = T + 1;                          // words per wavefront
+  constexpr int WPT = (kFpsCand / T * W + 255) / 256;   // words a thread reads at most
+  const int t = threadIdx.x, w = t >> 6, lane = t & 63;
+  const int G = (int)gridDim.x, words = G * 4 * W;
+  const int64_t stride = (int64_t)G * 256, j0 = (int64_t)blockIdx.x * 256 + t;
+  float4 p[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int64_t j = j0 + u * stride;
+    p[u] = j < a.M ? make_float4(a.pts[3 * j], a.pts[3 * j + 1], a.pts[3 * j + 2],
+                                 __int_as_float(0x7F800000))
+                   : make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  if (t == 0) {
+    s_pick[0] = make_float4(a.pts[3 * a.start], a.pts[3 * a.start + 1], a.pts[3 * a.start + 2],
+                            0.f);
+    s_pid[0] = (int32_t)a.start;
+    s_late = 0;
+  }
+  __syncthreads();
+  int np = 1;                                        // picks of the round before, in s_pick
+  int32_t done = 0;                                  // picks of the rounds before that
+  for (uint32_t round = 1;; ++round) {
+    if (blockIdx.x == 0)
+      for (int i = t; i < np; i += 256) a.chosen[done + i] = s_pid[i];
+    done += np;
+    if (done >= a.P) return;
+    for (int i = 0; i < np; ++i) {
+      const float4 c = s_pick[i];
+#pragma unroll
+      for (int u = 0; u < U; ++u) p[u].w = fminf(p[u].w, fps_d2(p[u], c));
+    }
+    // the thread's three largest keys: two it may publish and one it holds back
+    uint64_t k0 = 0, k1 = 0, k2 = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t j = j0 + u * stride;
+      uint64_t k = j < a.M ? fps_key(p[u].w, j) : 0;
+      const uint64_t m0 = max_u64(k0, k);
+      k = k0 < k ? k0 : k;
+      k0 = m0;
+      const uint64_t m1 = max_u64(k1, k);
+      k = k1 < k ? k1 : k;
+      k1 = m1;
+      k2 = max_u64(k2, k);
+    }
+    // the wavefront's T largest while the threads' two suffice, then the largest held back
+    uint64_t word = 0;
+    int left = 2;
+    bool open = true;
+#pragma unroll
+    for (int i = 0; i < T; ++i) {
+      const uint64_t m = fps_wave_max_key(k0);
+      open = open && __ballot(k0 == m && left == 0) == 0;
+      if (open && m != 0) {                          // uniform
+        if (lane == i) word = m;
+        if (k0 == m) {
+          k0 = k1;
+          k1 = k2;
+          k2 = 0;
+          --left;
+        }
+      }
+    }
+    const uint64_t rest = fps_wave_max_key(k0);
+    if (lane == T) word = rest;
+    const uint32_t tag = round & 3u;
+    uint64_t* row = a.rows + (size_t)(round % 3) * words;
+    if (lane < W) fps_st(row + ((int64_t)blockIdx.x * 4 + w) * W + lane, fps_tagged(word, tag));
+
+    // every wavefront's words
+    if (t == 0) s_n = 0;
+    uint64_t v[WPT], bound = 0;
+    bool late = false;
+#pragma unroll
+    for (int i = 0; i < WPT; ++i) v[i] = t + 256 * i < words ? fps_ld(row + t + 256 * i) : tag;
+    for (uint32_t n = 0;; ++n) {
+      bool wait = false;
+#pragma unroll
+      for (int i = 0; i < WPT; ++i)
+        if ((uint32_t)(v[i] & 3u) != tag) {
+          wait = true;
+          v[i] = fps_ld(row + t + 256 * i);
+        }
+      if (!wait) break;
+      if (n > kFpsSpin) {
+        late = true;
+        break;
+      }
+      __builtin_amdgcn_s_sleep(1);
+    }
+#pragma unroll
+    for (int i = 0; i < WPT; ++i) {
+      // the key again: distance bits above the inverted index (its top bit is always set)
+      v[i] = (v[i] >> 2) != 0 ? ((v[i] >> 33) << 32) | 0x80000000ull | ((v[i] >> 2) & 0x7FFFFFFFull)
+                              : 0;
+      if ((t + 256 * i) % W == T) {
+        bound = max_u64(bound, v[i]);
+        v[i] = 0;
+      }
+    }
+    if (late) s_late = 1;
+    bound = fps_wave_max_key(bound);
+    if (lane == 0) s_bound[w] = bound;
+    __syncthreads();
+    if (s_late) {
+      if (t == 0) __hip_atomic_store(a.fault, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return;
+    }
+    bound = max_u64(max_u64(s_bound[0], s_bound[1]), max_u64(s_bound[2], s_bound[3]));
+    // published points above the bound are the round's candidates
+#pragma unroll
+    for (int i = 0; i < WPT; ++i) {
+      const bool in = v[i] > bound;
+      const uint64_t m = __ballot(in);
+      if (m == 0) continue;
+      int base = 0;
+      if (lane == 0) base = atomicAdd(&s_n, __popcll(m));
+      base = __builtin_amdgcn_readfirstlane(base);
+      if (in) {
+        const int c = base + __popcll(m & ((1ull << lane) - 1ull));
+        const int64_t j = fps_index(v[i]);
+        s_key[c] = v[i];
+        s_pos[c] = make_float4(a.pts[3 * j], a.pts[3 * j + 1], a.pts[3 * j + 2], 0.f);
+      }
+    }
+    __syncthreads();
+    if (w == 0) {
+      const int n = s_n, most = min(a.P - done, kFpsCand);
+      int k;
+      if (n <= 64) k = fps_round_picks<1>(n, bound, most, lane, s_pos, s_key, s_pick, s_pid);
+      else if (n <= 128) k = fps_round_picks<2>(n, bound, most, lane, s_pos, s_key, s_pick, s_pid);
+      else if (n <= 256) k = fps_round_picks<4>(n, bound, most, lane, s_pos, s_key, s_pick, s_pid);
+      else if (n <= 512) k = fps_round_picks<8>(n, bound, most, lane, s_pos, s_key, s_pick, s_pid);
+      else k = fps_round_picks<kFpsCand / 64>(n, bound, most, lane, s_pos, s_key, s_pick, s_pid);
+      if (lane == 0) s_np = k;
+    }
+    __syncthreads();
+    np = s_np;
+  }
+}
+
 // pd[j] = (x_j, y_j, z_j, +inf): the points with their distance to the nearest pick so far
 __global__ __launch_bounds__(256) void k_fps_pack(const float* pts, int64_t M, float4* pd) {
   const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -227,9 +460,14 @@ __global__ __launch_bounds__(256) void k_fps_finish(const float* pts, const floa
   }
 }
 
-template <int U>
-void launch_fps(const FpsArgs& a, unsigned G, hipStream_t s) {
-  hipLaunchKernelGGL(k_fps<U>, dim3(G), dim3(256), 0, s, a);
+template <int T>
+static void launch_fps_rounds(const FpsRoundArgs& a, unsigned G, int64_t per, hipStream_t s) {
+  if (per <= 1) hipLaunchKernelGGL((k_fps_rounds<1, T>), dim3(G), dim3(256), 0, s, a);
+  else if (per <= 2) hipLaunchKernelGGL((k_fps_rounds<2, T>), dim3(G), dim3(256), 0, s, a);
+  else if (per <= 4) hipLaunchKernelGGL((k_fps_rounds<4, T>), dim3(G), dim3(256), 0, s, a);
+  else if (per <= 8) hipLaunchKernelGGL((k_fps_rounds<8, T>), dim3(G), dim3(256), 0, s, a);
+  else if (per <= 16) hipLaunchKernelGGL((k_fps_rounds<16, T>), dim3(G), dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((k_fps_rounds<kFpsMaxRegPts, T>), dim3(G), dim3(256), 0, s, a);
 }
 
 hipError_t launch_place_probes(const float* pts, const float* nrm, int64_t M, int32_t P,
@@ -243,19 +481,34 @@ hipError_t launch_place_probes(const float* pts, const float* nrm, int64_t M, in
                                                  kFpsMaxBlocks);
   const int64_t per = (M + 256 * (int64_t)G - 1) / (256 * (int64_t)G);
   int32_t* fault = reinterpret_cast<int32_t*>(sync + kFpsSyncRows * kFpsMaxBlocks);
-  hipError_t e = launch_fill_i32(reinterpret_cast<int32_t*>(sync), 0, 2 * kFpsSyncWords, s);
-  if (e != hipSuccess) return e;
-  const FpsArgs a{pts, reinterpret_cast<float4*>(packed), M, P, start, sync, fault, chosen};
-  if (per > kFpsMaxRegPts)
+  hipError_t e;
+  if (per > kFpsMaxRegPts) {
+    e = launch_fill_i32(reinterpret_cast<int32_t*>(sync), 0, 2 * kFpsSyncWords, s);
+    if (e != hipSuccess) return e;
+    const FpsArgs a{pts, reinterpret_cast<float4*>(packed), M, P, start, sync, fault, chosen};
     hipLaunchKernelGGL(k_fps_pack, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, s, pts, M,
                        a.pd);
-  if (per <= 1) launch_fps<1>(a, G, s);
-  else if (per <= 2) launch_fps<2>(a, G, s);
-  else if (per <= 4) launch_fps<4>(a, G, s);
-  else if (per <= 8) launch_fps<8>(a, G, s);
-  else if (per <= 16) launch_fps<16>(a, G, s);
-  else if (per <= kFpsMaxRegPts) launch_fps<kFpsMaxRegPts>(a, G, s);
-  else launch_fps<0>(a, G, s);
+    hipLaunchKernelGGL(k_fps, dim3(G), dim3(256), 0, s, a);
+  } else {
+    // more points of each wavefront where there are few wavefronts
+    const int T = G <= 16 ? 8 : 4;
+    // the rounds' words and the fault flag: in sync for one workgroup, else in the scratch
+    // of the streamed clouds (16 bytes a point, far more than the words of its workgroups)
+    const size_t words = (size_t)kFpsSyncRows * G * 4 * (T + 1);
+    uint64_t* rows = sync;
+    if (G > 1) {
+      rows = reinterpret_cast<uint64_t*>(packed);
+      fault = reinterpret_cast<int32_t*>(rows + words);
+      if ((words + 1) * sizeof(uint64_t) > (size_t)M * 16) return hipErrorInvalidValue;
+      e = launch_fill_i32(reinterpret_cast<int32_t*>(rows), 0, 2 * (words + 1), s);
+    } else {
+      e = launch_fill_i32(reinterpret_cast<int32_t*>(rows), 0, 2 * kFpsSyncWords, s);
+    }
+    if (e != hipSuccess) return e;
+    const FpsRoundArgs a{pts, M, P, start, rows, fault, chosen};
+    if (T == 8) launch_fps_rounds<8>(a, G, per, s);
+    else launch_fps_rounds<4>(a, G, per, s);
+  }
   hipLaunchKernelGGL(k_fps_finish, dim3((unsigned)std::min<int64_t>((P + 255) / 256, 1024)),
                      dim3(256), 0, s, pts, nrm, chosen, fault, P, offset, out);
   return hipGetLastError();
