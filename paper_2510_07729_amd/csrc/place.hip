@@ -3,18 +3,16 @@
 // normal, L_sops = L1(L_in, L_tr) + L1(O, O_tr) (probe textures towards the traced ones)
 // and L_lam = L1(R, 1) + L1(M, 0) (material regulariser), each with its gradient.
 //
-// FPS runs as one kernel of a few dozen workgroups that exchange each pick through memory:
-// each keeps its points and their squared distances d to the nearest pick so far in
+// FPS runs as one kernel of a few dozen workgroups that exchange their best points through
+// memory: each keeps its points and their squared distances d to the nearest pick so far in
 // registers (or, beyond 32 points per thread, as (x, y, z, d) in 16 bytes of device
-// memory), and
-// every pick is the maximum of 64-bit keys (distance bits, inverted index). A workgroup
-// publishes its own maximum, tagged with the pick number mod 4, in one of three rotating
-// rows of per-workgroup words and reads every other workgroup's word of that row until all
-// carry the pick's tag: one exchange per pick, with no counter, fence, clear or atomic
-// read-modify-write. Every wait is bounded; a workgroup that reaches the bound raises a
-// flag, and the probes of that call are then NaN. The losses are single coalesced passes
-// with per-workgroup FP64 partial sums added in a fixed order (the same inputs give the
-// same loss bit for bit).
+// memory), and every pick is the maximum of 64-bit keys (distance bits, inverted index).
+// Words are published tagged with the round (or pick) number mod 4, in one of three rotating
+// rows, and every workgroup reads the row until all its words carry the tag: no counter,
+// fence, clear or atomic read-modify-write is needed. Every wait is bounded; a workgroup that
+// reaches the bound raises a flag, and the probes of that call are then NaN. The losses are
+// single coalesced passes with per-workgroup FP64 partial sums added in a fixed order (the
+// same inputs give the same loss bit for bit).
 #include "sop_internal.hpp"
 
 namespace sopk {
@@ -72,11 +70,12 @@ __device__ __forceinline__ void fps_st(uint64_t* p, uint64_t v) {
 // poll of a row reads the same few cache lines from all workgroups, so the traffic of a
 // pick grows with the square of the workgroup count: a few dozen workgroups with several
 // points per thread (kFpsPts, up to kFpsMaxRegPts in registers) wait far less than one
-// point per thread on every compute unit. A wait gives up after kFpsSpin polls (about a
+// point per thread on every compute unit (in rounds, 4 / 8 / 16 points per thread: 65,536
+// samples 2.26 / 2.38 / 3.11 ms, 20,000 samples 0.94 / 1.23 / 1.45 ms). A wait gives up after kFpsSpin polls (about a
 // second; a normal wait is a few microseconds), which only workgroups that are not all
 // resident at once can reach: there are far fewer of them than compute units.
 constexpr int kFpsMaxBlocks = 64;
-constexpr int kFpsPts = 8;
+constexpr int kFpsPts = 4;
 constexpr int kFpsMaxRegPts = 32;
 constexpr uint32_t kFpsSpin = 1u << 20;
 static_assert(kFpsSyncWords == (size_t)kFpsSyncRows * kFpsMaxBlocks + 1, "fault flag after the rows");
@@ -191,9 +190,9 @@ __global__ __launch_bounds__(256) void k_fps(FpsArgs a) {
 // above B it is the next pick, exactly: each workgroup takes these picks for itself, lowering
 // the published points' distances, until the best falls to B, and then lowers its own points
 // by all the round's picks at once. The first pick of a round is always above B. On the
-// object's 65,536 samples a round takes 60 picks: 4096 picks in FPS_NOW us against 12,200 us
-// with an exchange per pick; what is left is the serial chain of a pick (a reduction over
-// one wavefront) and ~70 exchanges.
+// object's 65,536 samples a round takes 60 picks: 4096 picks in 1.71 ms against 12.2 ms with
+// an exchange per pick; what is left is the serial chain of a pick (~0.28 us: a reduction
+// over one wavefront) and ~70 rounds of ~8 us.
 //
 // Round r uses row r % 3 of published words with tag r & 3, as the picks of k_fps do: a word
 // of the row still holds round r - 3 or the zero of the launch until its wavefront writes
@@ -211,7 +210,7 @@ struct FpsRoundArgs {
 
 __device__ __forceinline__ uint32_t fps_wave_max(uint32_t v) {
 #define SOP_FPS_STEP(CTRL, ROWS) \
-  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, ROWS, 0xF, false))
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false))
   SOP_FPS_STEP(0xB1, 0xF);     // quad_perm [1,0,3,2]
   SOP_FPS_STEP(0x4E, 0xF);     // quad_perm [2,3,0,1]
   SOP_FPS_STEP(0x141, 0xF);    // row_half_mirror
@@ -230,62 +229,60 @@ __device__ __forceinline__ uint64_t fps_wave_max_key(uint64_t k) {
   return ((uint64_t)hi << 32) | fps_wave_max(top ? (uint32_t)k : 0u);
 }
 
-// The picks of one round over n candidates in LDS (pos, and low word of the key; key in
-// s_key), R per lane of one wavefront: up to `most` picks into s_pick and s_pid.
+// A candidate's place in the order of equal distances, with its slot in LDS: lower indices
+// first (20 bits: a cloud in registers has at most 2^19 points), never 0.
+__device__ __forceinline__ uint32_t fps_tie(uint64_t key, int slot) {
+  return (((uint32_t)key - 0x7FFFFFFFu - (0x80000000u - 0x80000u)) << 10) | (uint32_t)slot;
+}
+static_assert(kFpsCand <= 1 << 10 && 64 * 256 * kFpsMaxRegPts <= 1 << 19, "fps_tie");
+
+// The picks of one round over n candidates (positions and keys in LDS), R per lane of one
+// wavefront: up to `most` picks, their slots into s_slot. One pick after another is one serial
+// chain, so it is kept short: a reduction of the distance bits, one of the ties only where
+// two lanes tie, and the pick's position read back from its slot.
 template <int R>
 __device__ __forceinline__ int fps_round_picks(int n, uint64_t bound, int most, int lane,
                                                const float4* s_pos, const uint64_t* s_key,
-                                               float4* s_pick, int32_t* s_pid) {
+                                               int32_t* s_slot) {
   float4 p[R];
-  uint32_t inv[R];
+  uint32_t d[R], tie[R];                           // distance bits order as the distances
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int c = r * 64 + lane;
     p[r] = make_float4(0.f, 0.f, 0.f, 0.f);
-    inv[r] = 0;                                   // no candidate: never the largest key
+    d[r] = tie[r] = 0;                             // no candidate: never wins
     if (c < n) {
       p[r] = s_pos[c];
-      p[r].w = __uint_as_float((uint32_t)(s_key[c] >> 32));
-      inv[r] = (uint32_t)s_key[c];
+      d[r] = (uint32_t)(s_key[c] >> 32);
+      tie[r] = fps_tie(s_key[c], c);
     }
   }
-  int np = 0;
-  while (np < most) {
-    uint32_t d = 0;
+  const uint32_t bd = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(bound >> 32));
+  const uint32_t bt = (uint32_t)__builtin_amdgcn_readfirstlane(
+      bound != 0 ? (int)fps_tie(bound, kFpsCand - 1) : 0);
+  int np = 0, mine = 0;                            // lane i holds pick i of the last 64
+  for (;;) {
+    uint32_t v = 0;
 #pragma unroll
-    for (int r = 0; r < R; ++r) d = max(d, __float_as_uint(p[r].w));
-    const uint32_t top = fps_wave_max(d);
-    uint32_t q = 0;                                // largest inverted index at that distance
+    for (int r = 0; r < R; ++r) v = max(v, d[r]);
+    const uint32_t top = fps_wave_max(v);
+    uint32_t q = 0;
 #pragma unroll
-    for (int r = 0; r < R; ++r) q = max(q, __float_as_uint(p[r].w) == top ? inv[r] : 0u);
+    for (int r = 0; r < R; ++r) q = max(q, d[r] == top ? tie[r] : 0u);
     const uint64_t have = __ballot(q != 0);
-    uint32_t win;
-    if ((have & (have - 1)) == 0)
-      win = (uint32_t)__builtin_amdgcn_readlane((int)q, __builtin_ctzll(have | (1ull << 63)));
-    else
-      win = fps_wave_max(q);                       // equal distances: the lowest index
-    if ((((uint64_t)top << 32) | win) <= bound) break;
-    float x = 0.f, y = 0.f, z = 0.f;
+    uint32_t win = (uint32_t)__builtin_amdgcn_readlane((int)q, __builtin_ctzll(have));
+    if (have & (have - 1)) win = fps_wave_max(q);
+    // only a pick above everything held back is certain
+    if (np >= most || top < bd || (top == bd && win <= bt)) break;
+    const int slot = (int)(win & 1023u);
+    const float4 c = s_pos[slot];
+    mine = lane == (np & 63) ? slot : mine;
+    if ((np & 63) == 63) s_slot[np - 63 + lane] = mine;
 #pragma unroll
-    for (int r = 0; r < R; ++r)
-      if (inv[r] == win) {
-        x = p[r].x;
-        y = p[r].y;
-        z = p[r].z;
-      }
-    const int l = __builtin_ctzll(__ballot(q == win) | (1ull << 63));
-    const float4 c = make_float4(
-        __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l)),
-        __int_as_float(__builtin_amdgcn_readlane(__float_as_int(y), l)),
-        __int_as_float(__builtin_amdgcn_readlane(__float_as_int(z), l)), 0.f);
-#pragma unroll
-    for (int r = 0; r < R; ++r) p[r].w = fminf(p[r].w, fps_d2(p[r], c));
-    if (lane == 0) {
-      s_pick[np] = c;
-      s_pid[np] = (int32_t)(0xFFFFFFFFu - win);
-    }
+    for (int r = 0; r < R; ++r) d[r] = min(d[r], __float_as_uint(fps_d2(p[r], c)));
     ++np;
   }
+  if (lane < (np & 63)) s_slot[(np & ~63) + lane] = mine;
   return np;
 }
 
@@ -293,7 +290,7 @@ template <int U, int T>   // U points per thread, T published points per wavefro
 __global__ __launch_bounds__(256) void k_fps_rounds(FpsRoundArgs a) {
   __shared__ float4 s_pos[kFpsCand], s_pick[kFpsCand];
   __shared__ uint64_t s_key[kFpsCand], s_bound[4];
-  __shared__ int32_t s_pid[kFpsCand], s_n, s_np, s_late;
+  __shared__ int32_t s_pid[kFpsCand], s_slot[kFpsCand], s_n, s_np, s_late;
   constexpr int W = T + 1;                          // words per wavefront
   constexpr int WPT = (kFpsCand / T * W + 255) / 256;   // words a thread reads at most
   const int t = threadIdx.x, w = t >> 6, lane = t & 63;
@@ -424,15 +421,21 @@ __global__ __launch_bounds__(256) void k_fps_rounds(FpsRoundArgs a) {
     if (w == 0) {
       const int n = s_n, most = min(a.P - done, kFpsCand);
       int k;
-      if (n <= 64) k = fps_round_picks<1>(n, bound, most, lane, s_pos, s_key, s_pick, s_pid);
-      else if (n <= 128) k = fps_round_picks<2>(n, bound, most, lane, s_pos, s_key, s_pick, s_pid);
-      else if (n <= 256) k = fps_round_picks<4>(n, bound, most, lane, s_pos, s_key, s_pick, s_pid);
-      else if (n <= 512) k = fps_round_picks<8>(n, bound, most, lane, s_pos, s_key, s_pick, s_pid);
-      else k = fps_round_picks<kFpsCand / 64>(n, bound, most, lane, s_pos, s_key, s_pick, s_pid);
+      if (n <= 64) k = fps_round_picks<1>(n, bound, most, lane, s_pos, s_key, s_slot);
+      else if (n <= 128) k = fps_round_picks<2>(n, bound, most, lane, s_pos, s_key, s_slot);
+      else if (n <= 256) k = fps_round_picks<4>(n, bound, most, lane, s_pos, s_key, s_slot);
+      else if (n <= 512) k = fps_round_picks<8>(n, bound, most, lane, s_pos, s_key, s_slot);
+      else k = fps_round_picks<kFpsCand / 64>(n, bound, most, lane, s_pos, s_key, s_slot);
       if (lane == 0) s_np = k;
     }
     __syncthreads();
     np = s_np;
+    for (int i = t; i < np; i += 256) {
+      const int c = s_slot[i];
+      s_pick[i] = s_pos[c];
+      s_pid[i] = (int32_t)fps_index(s_key[c]);
+    }
+    __syncthreads();
   }
 }
 
