@@ -563,15 +563,25 @@ void set_dirs(sopk::ShadeArgs& a, const sop_envmap* env, const sop_shade_opts* o
   a.env_oct = env->layout == SOP_ENV_OCTAHEDRAL ? 1 : 0;
 }
 
-// the call's direction table, first piece of the workspace
-sop_status setup_dirs(sopk::ShadeArgs& a, Bump& b, const sop_shade_opts* o, hipStream_t s) {
+// the call's direction table, first piece of the workspace; with sorted, only the directions
+// along the hemisphere's Z curve are formed, there
+sop_status setup_dirs(sopk::ShadeArgs& a, Bump& b, const sop_shade_opts* o, hipStream_t s,
+                      double4* sorted = nullptr) {
   double4* tab = b.take<double4>((size_t)o->n_dirs);
   double2* col = b.take<double2>((size_t)a.W + 2);
   double2* row = b.take<double2>((size_t)a.H + 2);
-  a.dir_tab = tab;
+  a.dir_tab = sorted ? nullptr : tab;
   // the reference directions serve the equirectangular lookup only
   a.col_ref = a.env_oct ? nullptr : col;
   a.row_ref = a.env_oct ? nullptr : row;
+  if (sorted) {
+    a.dir_sorted = sorted;
+    SOP_HIP(sopk::launch_dir_sort(o->n_dirs, o->seed, o->rotate_per_point ? 1 : 0, sorted, s,
+                                  o->sampler == SOP_SAMPLER_COSINE ? 1 : 0, a.H, a.W,
+                                  a.env_oct ? nullptr : col, a.env_oct ? nullptr : row),
+            "direction table");
+    return SOP_OK;
+  }
   SOP_HIP(sopk::launch_dir_table(o->n_dirs, o->seed, o->rotate_per_point ? 1 : 0, a.H, a.W, tab,
                                  a.env_oct ? nullptr : col, a.env_oct ? nullptr : row, s),
           "direction table");
@@ -603,7 +613,10 @@ extern "C" sop_status sop_shade(const sop_plan* plan, const sop_probe_maps* maps
   uint16_t* frags = b.take<uint16_t>(sopk::mlp_frag_bytes() / sizeof(uint16_t));
   double4* sorted = b.take<double4>((size_t)opts->n_dirs);
   const EnvCdf cdf = carve_env_cdf(b, (size_t)env->height * (size_t)env->width);
-  if ((st = setup_dirs(a, b, opts, s)) != SOP_OK) return st;
+  // the uniform and the cosine-weighted set are read along the Z curve only
+  const bool fixed_set =
+      opts->sampler == SOP_SAMPLER_HAMMERSLEY || opts->sampler == SOP_SAMPLER_COSINE;
+  if ((st = setup_dirs(a, b, opts, s, fixed_set ? sorted : nullptr)) != SOP_OK) return st;
   if ((st = resolve_nb(plan, pts, nb, opts->k, opts->radius, b, s, &a.order, &a.nb_idx,
                        &a.nb_w, &kk)) != SOP_OK)
     return st;
@@ -633,10 +646,6 @@ extern "C" sop_status sop_shade(const sop_plan* plan, const sop_probe_maps* maps
     SOP_HIP(sopk::launch_shade_envis(a, kk, maps->format, s), "sop_shade");
   } else {
     a.cosine = opts->sampler == SOP_SAMPLER_COSINE ? 1 : 0;
-    SOP_HIP(sopk::launch_dir_sort(opts->n_dirs, opts->seed, opts->rotate_per_point ? 1 : 0,
-                                  sorted, s, a.cosine),
-            "sop_shade");
-    a.dir_sorted = sorted;
     SOP_HIP(sopk::launch_shade_fwd(a, kk, maps->format, s), "sop_shade");
   }
   return SOP_OK;
@@ -735,7 +744,8 @@ sop_status shade_backward_impl(const sop_plan* plan, const sop_probe_maps* maps,
   a.g_tex = g_tex;
   int32_t kk;
   Bump b{(char*)ws, 0, ws_bytes};
-  if ((st = setup_dirs(a, b, opts, s)) != SOP_OK) return st;
+  double4* sorted = b.take<double4>((size_t)opts->n_dirs);
+  if ((st = setup_dirs(a, b, opts, s, sorted)) != SOP_OK) return st;
   if ((st = resolve_nb(plan, pts, nb, opts->k, opts->radius, b, s, &a.order, &a.nb_idx,
                        &a.nb_w, &kk)) != SOP_OK)
     return st;
@@ -759,11 +769,6 @@ sop_status shade_backward_impl(const sop_plan* plan, const sop_probe_maps* maps,
     a.det_nt = dl.nt;
     a.det_ne = dl.ne;
   }
-  double4* sorted = b.take<double4>((size_t)opts->n_dirs);
-  SOP_HIP(sopk::launch_dir_sort(opts->n_dirs, opts->seed, opts->rotate_per_point ? 1 : 0,
-                                sorted, s),
-          fn);
-  a.dir_sorted = sorted;
   const bool blocks = !det && g_env && env_blocks_fit(env->height, env->width) &&
                       sopk::shade_bwd_batched(maps->res, kk);
   if (blocks) {

@@ -274,7 +274,7 @@ __device__ __forceinline__ void eval_sample(const ShadeArgs& a, const PointState
   // the adjoint walks the directions along the Z curve over the hemisphere (dir_sorted):
   // a wavefront's 64 lanes then look into one compact region, and its gathers share more
   // cache lines than in the table's own order (the sum over directions is order-free)
-  const double4 e = a.dir_sorted ? a.dir_sorted[j] : a.dir_tab[j];
+  const double4 e = a.dir_sorted[j];
   const double da = e.x * ps.cr - e.y * ps.sr;
   const double db = e.x * ps.sr + e.y * ps.cr;
   world_dir64(ps.F, da, db, e.z, s.w64);
@@ -2032,11 +2032,8 @@ hipError_t launch_env_blk_finish(const float* blk, int32_t bw, int32_t bh, int32
 // per-call tables: directions, and reference directions of the environment's texel
 // columns (phi_i = 2 pi (i + 0.5)/W - pi, i in [-1, W]) and rows (theta_j = pi (j + 0.5)/H,
 // j in [-1, H]), all in FP64
-__global__ __launch_bounds__(256) void k_dir_table(int32_t S, uint32_t rho, double4* tab,
-                                                   int32_t H, int32_t W, double2* col_ref,
-                                                   double2* row_ref) {
-  const int32_t j = blockIdx.x * 256 + threadIdx.x;
-  if (j < S) tab[j] = dir_entry(j, S, rho);
+__device__ __forceinline__ void env_refs(int32_t j, int32_t H, int32_t W, double2* col_ref,
+                                         double2* row_ref) {
   if (col_ref && j < W + 2) {
     double sn, cs;
     sincospi(2.0 * ((double)(j - 1) + 0.5) / (double)W - 1.0, &sn, &cs);
@@ -2047,6 +2044,14 @@ __global__ __launch_bounds__(256) void k_dir_table(int32_t S, uint32_t rho, doub
     sincospi(((double)(j - 1) + 0.5) / (double)H, &sn, &cs);
     row_ref[j] = make_double2(cs, sn);
   }
+}
+
+__global__ __launch_bounds__(256) void k_dir_table(int32_t S, uint32_t rho, double4* tab,
+                                                   int32_t H, int32_t W, double2* col_ref,
+                                                   double2* row_ref) {
+  const int32_t j = blockIdx.x * 256 + threadIdx.x;
+  if (j < S) tab[j] = dir_entry(j, S, rho);
+  env_refs(j, H, W, col_ref, row_ref);
 }
 
 // 20-bit Morton code of two 10-bit coordinates
@@ -2064,16 +2069,29 @@ __device__ __forceinline__ uint32_t morton2(uint32_t x, uint32_t y) {
 
 // The S directions of the call (dir_entry) ordered by the Z curve of their position on the
 // hemispherical octahedral square (u, v) = (x + y, x - y) / (|x| + |y| + z) at 10 bits per
-// axis, ties by index: a bitonic sort of (code << 12 | j) in one workgroup (S <= 4096).
+// axis, ties by index, in the first workgroup: up to kDirCount directions are placed by
+// counting the smaller keys, more by a bitonic sort of (code << 12 | j) (S <= 4096). The
+// other workgroups form the environment's reference directions (see k_dir_table), so that a
+// shading call makes its tables in one launch.
+constexpr int kDirCount = 256;
 __global__ __launch_bounds__(1024) void k_dir_sort(int32_t S, uint32_t rho, double4* sorted,
-                                                  int32_t cosine) {
-  __shared__ uint32_t key[SOP_MAX_DIRS];
+                                                  int32_t cosine, int32_t H, int32_t W,
+                                                  double2* col_ref, double2* row_ref) {
+  __shared__ __attribute__((aligned(16))) uint32_t key[SOP_MAX_DIRS];
+  if (blockIdx.x > 0) {
+    const int32_t j = ((int32_t)blockIdx.x - 1) * 1024 + (int32_t)threadIdx.x;
+    env_refs(j, H, W, col_ref, row_ref);
+    return;
+  }
+  const int tid = threadIdx.x;
   int n = 1;
   while (n < S) n <<= 1;
-  for (int i = threadIdx.x; i < n; i += 1024) {
+  n = max(n, 4);
+  double4 e = make_double4(0.0, 0.0, 0.0, 0.0);
+  for (int i = tid; i < n; i += 1024) {
     uint32_t kv = 0xFFFFFFFFu;
     if (i < S) {
-      const double4 e = dir_entry(i, S, rho, cosine != 0);
+      e = dir_entry(i, S, rho, cosine != 0);
       const double l1 = fabs(e.x) + fabs(e.y) + e.z;
       const double u = (e.x + e.y) / l1, v = (e.x - e.y) / l1;
       const uint32_t qu = (uint32_t)fmin(fmax((u + 1.0) * 512.0, 0.0), 1023.0);
@@ -2083,9 +2101,20 @@ __global__ __launch_bounds__(1024) void k_dir_sort(int32_t S, uint32_t rho, doub
     key[i] = kv;
   }
   __syncthreads();
+  if (S <= kDirCount) {
+    if (tid >= S) return;
+    const uint32_t k = key[tid];
+    int c = 0;
+    for (int j = 0; j < n; j += 4) {
+      const uint4 q = *reinterpret_cast<const uint4*>(key + j);
+      c += (q.x < k) + (q.y < k) + (q.z < k) + (q.w < k);
+    }
+    sorted[c] = e;
+    return;
+  }
   for (int size = 2; size <= n; size <<= 1)
     for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      for (int t = threadIdx.x; t < n / 2; t += 1024) {
+      for (int t = tid; t < n / 2; t += 1024) {
         const int i = 2 * stride * (t / stride) + (t % stride), j = i + stride;
         const uint32_t x = key[i], y = key[j];
         if ((x > y) == ((i & size) == 0)) {
@@ -2095,15 +2124,18 @@ __global__ __launch_bounds__(1024) void k_dir_sort(int32_t S, uint32_t rho, doub
       }
       __syncthreads();
     }
-  for (int i = threadIdx.x; i < S; i += 1024)
+  for (int i = tid; i < S; i += 1024)
     sorted[i] = dir_entry((int)(key[i] & 0xFFFu), S, rho, cosine != 0);
 }
 
 hipError_t launch_dir_sort(int32_t S, uint32_t seed, int32_t per_point, double4* sorted,
-                           hipStream_t s, int32_t cosine) {
+                           hipStream_t s, int32_t cosine, int32_t H, int32_t W, double2* col_ref,
+                           double2* row_ref) {
   if (S < 1 || S > SOP_MAX_DIRS || !sorted) return hipErrorInvalidValue;
   const uint32_t rho = per_point ? 0u : rotation24(seed, false, 0u);
-  hipLaunchKernelGGL(k_dir_sort, dim3(1), dim3(1024), 0, s, S, rho, sorted, cosine);
+  const int32_t n = max(col_ref ? W + 2 : 0, row_ref ? H + 2 : 0);
+  hipLaunchKernelGGL(k_dir_sort, dim3(1 + (n + 1023) / 1024), dim3(1024), 0, s, S, rho, sorted,
+                     cosine, H, W, col_ref, row_ref);
   return hipGetLastError();
 }
 

@@ -157,9 +157,11 @@ hipError_t launch_adam(float* p, float* m, float* v, const float* g, int64_t n, 
 // per-call direction table: dir_entry(j, S, rho) with rho of the call (0 when per point)
 hipError_t launch_dir_table(int32_t S, uint32_t seed, int32_t per_point, int32_t H, int32_t W,
                             double4* tab, double2* col_ref, double2* row_ref, hipStream_t s);
-// the call's directions in the order of a Z curve over the hemisphere (shading forward)
+// the call's directions in the order of a Z curve over the hemisphere (shading forward and
+// adjoint), and the environment's reference directions when their arrays are given
 hipError_t launch_dir_sort(int32_t S, uint32_t seed, int32_t per_point, double4* sorted,
-                           hipStream_t s, int32_t cosine = 0);
+                           hipStream_t s, int32_t cosine, int32_t H, int32_t W, double2* col_ref,
+                           double2* row_ref);
 hipError_t launch_shade_fwd(const ShadeArgs& a, int32_t k, int32_t format, hipStream_t s);
 hipError_t launch_shade_bwd(const ShadeArgs& a, int32_t k, int32_t format, hipStream_t s);
 // whether launch_shade_bwd takes the batched kernel (the one that reads a.env_blk)

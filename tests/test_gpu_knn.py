@@ -77,8 +77,9 @@ def spread(v):
     (64, 20_000, 0.3),                         # cells of ~2000 points: bins
     (64, 40_000, 0.2),                         # cells beyond the sorted size stay whole
     (4096, 60_000, 2.0), (16_384, 60_000, 2.0),
-    (64, 5000, 0.0), (4096, 3000, 1e-4),       # one place: a bin above the counted size
-    (64, 4096, 0.25), (64, 257, 0.1), (64, 256, 0.1),
+    (64, 5000, 0.0), (64, 4097, 1e-4), (4096, 3000, 1e-4),   # one place: a crowded bin
+    (64, 4096, 0.25), (64, 257, 0.1), (64, 256, 0.1), (64, 6000, 0.05), (64, 1, 1.0),
+    (64, 6000, 0.4), (512, 5000, 0.3),         # cells of 257 points and more, and fewer
 ])
 def test_processing_order(P, N, side):
     import torch
