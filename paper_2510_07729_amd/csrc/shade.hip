@@ -74,6 +74,18 @@ __device__ __forceinline__ bool load_point(const ShadeArgs& a, int64_t wv, Point
   return true;
 }
 
+// entry e of the direction table, turned by the point's rotation (where the call rotates per
+// point) into the frame of its normal
+__device__ __forceinline__ void rotated_dir(const ShadeArgs& a, const PointState& ps,
+                                            const double4& e, double w[3]) {
+  double x = e.x, y = e.y;
+  if (a.per_point) {                                // uniform
+    x = e.x * ps.cr - e.y * ps.sr;
+    y = e.x * ps.sr + e.y * ps.cr;
+  }
+  world_dir64(ps.F, x, y, e.z, w);
+}
+
 // Neighbour list of a point: KT > 0 keeps K entries in registers (scalar), KT == 0 reads the
 // list inside the loop for a run-time K.
 template <int KT>
@@ -229,14 +241,14 @@ __device__ __forceinline__ void eval_at(const ShadeArgs& a, const PointState& ps
         const float4 x0 = load_texel(T, (size_t)ad0), x1 = load_texel(T, (size_t)ad1);
         const float4 x2 = load_texel(T, (size_t)ad2), x3 = load_texel(T, (size_t)ad3);
         const float e0 = wk * c0, e1 = wk * c1, e2 = wk * c2, e3 = wk * c3;
-        ev.x += e0 * x0.x + e2 * x2.x;
-        ev.y += e0 * x0.y + e2 * x2.y;
-        ev.z += e0 * x0.z + e2 * x2.z;
-        ev.w += e0 * x0.w + e2 * x2.w;
-        od.x += e1 * x1.x + e3 * x3.x;
-        od.y += e1 * x1.y + e3 * x3.y;
-        od.z += e1 * x1.z + e3 * x3.z;
-        od.w += e1 * x1.w + e3 * x3.w;
+        ev.x = fmaf(e0, x0.x, fmaf(e2, x2.x, ev.x));
+        ev.y = fmaf(e0, x0.y, fmaf(e2, x2.y, ev.y));
+        ev.z = fmaf(e0, x0.z, fmaf(e2, x2.z, ev.z));
+        ev.w = fmaf(e0, x0.w, fmaf(e2, x2.w, ev.w));
+        od.x = fmaf(e1, x1.x, fmaf(e3, x3.x, od.x));
+        od.y = fmaf(e1, x1.y, fmaf(e3, x3.y, od.y));
+        od.z = fmaf(e1, x1.z, fmaf(e3, x3.z, od.z));
+        od.w = fmaf(e1, x1.w, fmaf(e3, x3.w, od.w));
       }
       const float4 keep = odd ? od : ev, send = odd ? ev : od;
       s.Lin[0] = keep.x + pair_swap<PAIR>(send.x);
@@ -275,9 +287,7 @@ __device__ __forceinline__ void eval_sample(const ShadeArgs& a, const PointState
   // a wavefront's 64 lanes then look into one compact region, and its gathers share more
   // cache lines than in the table's own order (the sum over directions is order-free)
   const double4 e = a.dir_sorted[j];
-  const double da = e.x * ps.cr - e.y * ps.sr;
-  const double db = e.x * ps.sr + e.y * ps.cr;
-  world_dir64(ps.F, da, db, e.z, s.w64);
+  rotated_dir(a, ps, e, s.w64);
   s.w = mk3((float)s.w64[0], (float)s.w64[1], (float)s.w64[2]);
   s.ct = (float)e.z;
   eval_at<KT, TexT, EO, 1>(a, ps, nb, k, s);
@@ -325,64 +335,135 @@ __device__ __forceinline__ void order_by_probe(Neighbors<KT>& nb) {
 }
 
 // Shading forward in the cluster layout: a wavefront takes 8 consecutive points of the
-// processing order, 8 lanes per point, and lane q of a point takes directions q, q + 8, ...
-// of the call's direction table sorted along a Z curve over the hemisphere (dir_sorted),
-// so that at every step the 8 directions of a point are close together, and the 8 points,
-// whose normals are close (the processing order groups them by probe-grid cell) and whose
-// neighbour lists mostly coincide (ordered by probe index), look the same way, and the
-// per-point work (neighbour lists, frame, material, the final sums) is shared by 8 lanes
-// instead of 64. On the object workload this layout takes 0.95 ms against 1.19 ms for one
-// point per wavefront; its texture units stay ~86% busy (32 16-byte gathers per sample),
-// so the texture path remains the bound. The sum over a point's
-// directions is order-free (Eq. 7); the 8 lanes' partial sums meet by shuffles.
+// processing order, 8 lanes per point. At every step a point's lanes take 8 consecutive
+// directions of the call's table, sorted along a Z curve over the hemisphere (dir_sorted), so
+// that they are close together, and the 8 points, whose normals are close (the processing
+// order groups them by place) and whose neighbour lists mostly coincide (ordered by probe
+// index), look the same way.
+//
+// The texture path is the bound (its data unit is busy 86% of the time on the object
+// workload, the vector ALUs issue ~60%; on a frame of half-precision maps it is the other way
+// round, ~80% ALU): it serves four lanes of a gather per cycle if they read one cache line.
+// So the two lanes of a pair (same point, split taps: eval_at) are neighbours, the next
+// pair is the next point, which mostly reads the same texels, and only then come the other
+// directions: lane = 16 (direction / 2) + 2 point + (direction & 1). With the directions of
+// a point in neighbouring lanes instead, a load made 37.5 cache accesses, now 27.5.
+//
+// What a sample reads of its point (frame, view, material) stays in LDS instead of in every
+// one of the 8 lanes' registers: 123 registers and four wavefronts per SIMD instead of 166
+// and three. Where every point has a rotation of its own, neighbouring points share nothing
+// and a fourth wavefront only costs cache (1.17 against 1.03 ms on the object workload), so
+// the launch holds those calls at three by their LDS.
+// 200k points, 4096 probes, S = 128, K = 8: 0.84 -> 0.74 ms; a 1920x1080 frame, half
+// maps, S = 64: 3.82 -> 2.93 ms. The sum over a point's directions is order-free (Eq. 7); the 8
+// lanes' partial sums meet by shuffles.
 constexpr int kFwdLanes = 8;          // lanes per point (points per wavefront: 64 / kFwdLanes)
+struct __attribute__((aligned(16))) FwdPoint {   // 144 bytes: 8 points on distinct LDS banks
+  double t[3], b[3], n[3], v[3];                 // frame and view
+  double cr, sr;                                 // rotation
+  float al[3], m, a2, k, one_m_k, vis;           // material (see Material)
+};
+constexpr size_t kFwdRotLds = 45000;  // bytes that leave room for three workgroups per unit
 template <int KT, typename TexT, bool EO = false, bool COS = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_shade_fwd_cl(ShadeArgs a, int32_t k) {
   constexpr int PPW = 64 / kFwdLanes;
-  const int lane = threadIdx.x & 63, q = lane % kFwdLanes;
+  __shared__ FwdPoint s_pt[kWavesPerBlock][PPW];
+  const int lane = threadIdx.x & 63, q = (lane >> 4) * 2 + (lane & 1);
   const int64_t wv = die_block() * kWavesPerBlock + wave_id_uniform();
   if (wv * PPW >= a.n) return;                          // uniform over the wavefront
-  const int64_t slot = wv * PPW + lane / kFwdLanes;
-  PointState ps;
-  const bool valid = slot < a.n && load_point<false>(a, slot, ps);
+  const int pi = (lane >> 1) & 7;
+  const int64_t slot = wv * PPW + pi;
+  FwdPoint& fp = s_pt[threadIdx.x >> 6][pi];
+  bool valid;
+  int64_t pidx = 0;
+  Neighbors<KT> nb;
+  {
+    PointState ps;
+    valid = slot < a.n && load_point<false>(a, slot, ps);
+    if (valid) {
+      pidx = ps.p;
+      nb.load(a, ps.p, k);
+      order_by_probe<KT>(nb);
+      if (q == 0) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          fp.t[c] = ps.F.t[c];
+          fp.b[c] = ps.F.b[c];
+          fp.n[c] = ps.F.n[c];
+          fp.v[c] = ps.v64[c];
+        }
+        fp.cr = ps.cr;
+        fp.sr = ps.sr;
+        fp.al[0] = ps.M.a.x;
+        fp.al[1] = ps.M.a.y;
+        fp.al[2] = ps.M.a.z;
+        fp.m = ps.M.m;
+        fp.a2 = ps.M.a2;
+        fp.k = ps.M.k;
+        fp.one_m_k = ps.M.one_m_k;
+        fp.vis = ps.M.vis;
+      }
+    }
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   float acc[3] = {0.0f, 0.0f, 0.0f}, acc_e[3] = {0.0f, 0.0f, 0.0f};
+  PointState ps;
+  ps.p = pidx;
   if (valid) {
-    Neighbors<KT> nb;
-    nb.load(a, ps.p, k);
-    order_by_probe<KT>(nb);
-    const float al[3] = {ps.M.a.x, ps.M.a.y, ps.M.a.z};
     for (int i = q; i < a.S; i += kFwdLanes) {
+      // the compiler would otherwise lift the point's data back into registers
+      asm volatile("" ::: "memory");
       const double4 e = a.dir_sorted[i];
       Sample s;
-      const double da = e.x * ps.cr - e.y * ps.sr;
-      const double db = e.x * ps.sr + e.y * ps.cr;
-      world_dir64(ps.F, da, db, e.z, s.w64);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        ps.F.t[c] = fp.t[c];
+        ps.F.b[c] = fp.b[c];
+        ps.F.n[c] = fp.n[c];
+      }
+      ps.cr = fp.cr;
+      ps.sr = fp.sr;
+      rotated_dir(a, ps, e, s.w64);
       s.w = mk3((float)s.w64[0], (float)s.w64[1], (float)s.w64[2]);
       s.ct = (float)e.z;
-      eval_at<KT, TexT, EO, 1>(a, ps, nb, k, s);
-      const BrdfTerms bt = brdf_terms(ps.M, half_geom(ps.n64, ps.v64, s.w64), s.ct);
-      // the cosine-weighted set weighs each sample by 1/(2 cos) relative to 2 pi/S
       const float wj = COS ? (float)e.w : 1.0f;
+      eval_at<KT, TexT, EO, 1>(a, ps, nb, k, s);
+      asm volatile("" ::: "memory");
+      const double n64[3] = {fp.n[0], fp.n[1], fp.n[2]}, v64[3] = {fp.v[0], fp.v[1], fp.v[2]};
+      Material M;
+      M.m = fp.m;
+      M.a2 = fp.a2;
+      M.k = fp.k;
+      M.one_m_k = fp.one_m_k;
+      M.vis = fp.vis;
+      const BrdfTerms bt = brdf_terms(M, half_geom(n64, v64, s.w64), s.ct);
+      // the cosine-weighted set weighs each sample by 1/(2 cos) relative to 2 pi/S
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
         const float Li = (1.0f - s.O) * s.Le[c] + s.Lin[c];
         if constexpr (COS) {
-          acc[c] += fcos(ps.M, bt, al[c], s.ct) * Li * wj;
+          acc[c] += fcos(M, bt, fp.al[c], s.ct) * Li * wj;
           acc_e[c] += Li * s.ct * wj;
         } else {
-          acc[c] += fcos(ps.M, bt, al[c], s.ct) * Li;
+          acc[c] += fcos(M, bt, fp.al[c], s.ct) * Li;
           acc_e[c] += Li * s.ct;
         }
       }
     }
   }
 #pragma unroll
-  for (int c = 0; c < 3; ++c)
+  for (int c = 0; c < 3; ++c) {
+    // the lanes of a point: l ^ 1, l ^ 16, l ^ 32
+    acc[c] += pair_swap<1>(acc[c]);
+    acc_e[c] += pair_swap<1>(acc_e[c]);
 #pragma unroll
-    for (int o = 1; o < kFwdLanes; o <<= 1) {
+    for (int o = 16; o < 64; o <<= 1) {
       acc[c] += __shfl_xor(acc[c], o);
       acc_e[c] += __shfl_xor(acc_e[c], o);
     }
+  }
   if (!valid || q != 0) return;
 #pragma unroll
   for (int c = 0; c < 3; ++c) a.rgb[3 * ps.p + c] = acc[c] * a.scale;
@@ -407,10 +488,8 @@ __global__ __launch_bounds__(256) void k_shade_traced(ShadeArgs a) {
     const float4* tr = a.traced + ps.p * a.S;
     for (int j = li; j < a.S; j += L) {
       const double4 e = a.dir_tab[j];
-      const double da = e.x * ps.cr - e.y * ps.sr;
-      const double db = e.x * ps.sr + e.y * ps.cr;
       double w64[3];
-      world_dir64(ps.F, da, db, e.z, w64);
+      rotated_dir(a, ps, e, w64);
       const float ct = (float)e.z;
       const EnvTaps et = env_taps_of<EO>(a, w64);
       float Le[3] = {0.0f, 0.0f, 0.0f};
@@ -1118,15 +1197,17 @@ __device__ __forceinline__ void sample_adjoint(const ShadeArgs& a, const PointSt
   eval_sample<KT, TexT, EO>(a, ps, nb, k, j, s);
   const BrdfTerms bt = brdf_terms(M, half_geom(ps.n64, ps.v64, s.w64), s.ct);
   const float om5 = 1.0f - bt.x5;
-  // dD/dalpha = 2 alpha (1 - NoH^2 - alpha^2 NoH^2) / (pi q^3)
-  const float dD = 2.0f * M.alpha * (bt.one_m - M.a2 * bt.NoH2) / (kPi * bt.q * bt.q * bt.q);
-  const float denL = s.ct * M.one_m_k + M.k, denV = M.NoV * M.one_m_k + M.k;
-  const float dG1L = -s.ct * (1.0f - s.ct) / (denL * denL);
-  const float dG1V = -M.NoV * (1.0f - M.NoV) / (denV * denV);
+  // D = alpha^2 / (pi q^2), dD/dalpha = 2 alpha (1 - NoH^2 - alpha^2 NoH^2) / (pi q^3)
+  const float D = (M.a2 * bt.iq) * bt.iq * kInvPi;
+  const float dD =
+      2.0f * (M.alpha * bt.iq) * ((bt.one_m - M.a2 * bt.NoH2) * bt.iq) * bt.iq * kInvPi;
+  const float iV = M.g1v / M.NoV;                    // 1 / (NoV (1 - k) + k)
+  const float dG1L = -s.ct * (1.0f - s.ct) * (bt.iL * bt.iL);
+  const float dG1V = -M.NoV * (1.0f - M.NoV) * (iV * iV);
   const float G = bt.G1L * M.g1v;
   const float dG = 0.5f * (dG1L * M.g1v + bt.G1L * dG1V);
   const float i4nv = 1.0f / (4.0f * M.NoV);
-  const float drough = i4nv * (dD * G + bt.D * dG) * 2.0f * M.r;
+  const float drough = i4nv * (dD * G + D * dG) * 2.0f * M.r;
   r.go = 0.0f;
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
@@ -1724,17 +1805,18 @@ template <int KT, bool EO>
 static void launch_fwd_e(const ShadeArgs& a, int32_t k, int32_t format, hipStream_t s) {
   constexpr int per_block = kWavesPerBlock * (64 / kFwdLanes);
   const dim3 grid((unsigned)((a.n + per_block - 1) / per_block));
+  const size_t lds = a.per_point ? kFwdRotLds : 0;
   if (a.cosine) {
     if (format == SOP_TEXEL_F16)
-      hipLaunchKernelGGL((k_shade_fwd_cl<KT, uint2, EO, true>), grid, dim3(256), 0, s, a, k);
+      hipLaunchKernelGGL((k_shade_fwd_cl<KT, uint2, EO, true>), grid, dim3(256), lds, s, a, k);
     else
-      hipLaunchKernelGGL((k_shade_fwd_cl<KT, float4, EO, true>), grid, dim3(256), 0, s, a, k);
+      hipLaunchKernelGGL((k_shade_fwd_cl<KT, float4, EO, true>), grid, dim3(256), lds, s, a, k);
     return;
   }
   if (format == SOP_TEXEL_F16)
-    hipLaunchKernelGGL((k_shade_fwd_cl<KT, uint2, EO>), grid, dim3(256), 0, s, a, k);
+    hipLaunchKernelGGL((k_shade_fwd_cl<KT, uint2, EO>), grid, dim3(256), lds, s, a, k);
   else
-    hipLaunchKernelGGL((k_shade_fwd_cl<KT, float4, EO>), grid, dim3(256), 0, s, a, k);
+    hipLaunchKernelGGL((k_shade_fwd_cl<KT, float4, EO>), grid, dim3(256), lds, s, a, k);
 }
 
 template <int KT>

@@ -29,6 +29,22 @@ __device__ __forceinline__ v3 cross(v3 a, v3 b) {
 __device__ __forceinline__ float sgn1(float x) { return x < 0.0f ? -1.0f : 1.0f; }
 
 // ----------------------------------------------------------------------------------------
+// Reciprocals without the scaling and fix-up steps of an IEEE division: the hardware
+// estimate and Newton steps, 3 instructions (FP32, within an ulp) and 5 (FP64, within a few
+// ulps) instead of about 10 and 12. A sample of the shading estimate takes five of one kind
+// and three of the other. Arguments are finite and normal; 0 gives NaN (as 0 / 0 would).
+// ----------------------------------------------------------------------------------------
+__device__ __forceinline__ float rcp32(float x) {
+  const float r = __builtin_amdgcn_rcpf(x);
+  return fmaf(fmaf(-x, r, 1.0f), r, r);
+}
+__device__ __forceinline__ double rcp64(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(fma(-x, r, 1.0), r, r);
+  return fma(fma(-x, r, 1.0), r, r);
+}
+
+// ----------------------------------------------------------------------------------------
 // Direction set (Eq. 7: S_r rays from a Hammersley set). Rotation: pcg hash of Jarzynski &
 // Olano (JCGT 2020), 24 bits.
 // ----------------------------------------------------------------------------------------
@@ -118,45 +134,6 @@ __device__ __forceinline__ void oct_wrap(int i, int j, int R, int& oi, int& oj) 
   oj = j;
 }
 
-__device__ __forceinline__ Taps oct_taps(v3 w, int R, float halfR) {
-  const float s = fabsf(w.x) + fabsf(w.y) + fabsf(w.z);
-  const float inv = 1.0f / s;
-  float px = w.x * inv, py = w.y * inv;
-  if (w.z < 0.0f) {
-    const float fx = (1.0f - fabsf(py)) * sgn1(px);
-    const float fy = (1.0f - fabsf(px)) * sgn1(py);
-    px = fx;
-    py = fy;
-  }
-  // clamp to [-0.5, R-0.5] (also maps NaN there): every tap index stays in [-1, R]
-  const float hi = 2.0f * halfR - 0.5f;
-  const float cu = fminf(fmaxf((px + 1.0f) * halfR - 0.5f, -0.5f), hi);
-  const float cv = fminf(fmaxf((py + 1.0f) * halfR - 0.5f, -0.5f), hi);
-  const float i0f = floorf(cu), j0f = floorf(cv);
-  const float fx = cu - i0f, fy = cv - j0f;
-  const int i0 = (int)i0f, j0 = (int)j0f;
-  Taps t;
-  t.i0 = i0;
-  t.j0 = j0;
-  int ii, jj;
-  oct_wrap(i0, j0, R, ii, jj);
-  t.off[0] = jj * R + ii;
-  oct_wrap(i0 + 1, j0, R, ii, jj);
-  t.off[1] = jj * R + ii;
-  oct_wrap(i0, j0 + 1, R, ii, jj);
-  t.off[2] = jj * R + ii;
-  oct_wrap(i0 + 1, j0 + 1, R, ii, jj);
-  t.off[3] = jj * R + ii;
-  t.w[0] = (1.0f - fx) * (1.0f - fy);
-  t.w[1] = fx * (1.0f - fy);
-  t.w[2] = (1.0f - fx) * fy;
-  t.w[3] = fx * fy;
-  return t;
-}
-
-// Same taps from an FP64 direction: the bilinear weights of the probe textures then carry
-// no FP32 coordinate rounding (it would be amplified in the texture gradient of entries
-// that receive only small weights).
 // direction of texture coordinate (u, v) in texel units of an R x R octahedral map, FP64
 __device__ __forceinline__ void oct_decode64(double u, double v, int R, double w[3]) {
   double px = 2.0 * u / (double)R - 1.0, py = 2.0 * v / (double)R - 1.0;
@@ -173,34 +150,38 @@ __device__ __forceinline__ void oct_decode64(double u, double v, int R, double w
   w[2] = z * il;
 }
 
+// The taps come from an FP64 direction: the bilinear weights of the probe textures then carry
+// no FP32 coordinate rounding (it would be amplified in the texture gradient of entries
+// that receive only small weights).
 __device__ __forceinline__ Taps oct_taps64(const double w[3], int R) {
-  const double s = fabs(w[0]) + fabs(w[1]) + fabs(w[2]);
-  const double inv = 1.0 / s;
+  const double inv = rcp64(fabs(w[0]) + fabs(w[1]) + fabs(w[2]));
   double px = w[0] * inv, py = w[1] * inv;
   if (w[2] < 0.0) {
-    const double fx = (1.0 - fabs(py)) * (px < 0.0 ? -1.0 : 1.0);
-    const double fy = (1.0 - fabs(px)) * (py < 0.0 ? -1.0 : 1.0);
+    const double fx = copysign(1.0 - fabs(py), px);
+    const double fy = copysign(1.0 - fabs(px), py);
     px = fx;
     py = fy;
   }
+  // clamped to [-0.5, R - 0.5] (NaN included): every tap index stays in [-1, R]
   const double halfR = 0.5 * (double)R, hi = (double)R - 0.5;
-  const double cu = fmin(fmax((px + 1.0) * halfR - 0.5, -0.5), hi);
-  const double cv = fmin(fmax((py + 1.0) * halfR - 0.5, -0.5), hi);
+  const double cu = fmin(fmax(fma(px, halfR, halfR - 0.5), -0.5), hi);
+  const double cv = fmin(fmax(fma(py, halfR, halfR - 0.5), -0.5), hi);
   const double i0f = floor(cu), j0f = floor(cv);
   const double fx = cu - i0f, fy = cv - j0f;
   const int i0 = (int)i0f, j0 = (int)j0f;
   Taps t;
   t.i0 = i0;
   t.j0 = j0;
-  int ii, jj;
-  oct_wrap(i0, j0, R, ii, jj);
-  t.off[0] = jj * R + ii;
-  oct_wrap(i0 + 1, j0, R, ii, jj);
-  t.off[1] = jj * R + ii;
-  oct_wrap(i0, j0 + 1, R, ii, jj);
-  t.off[2] = jj * R + ii;
-  oct_wrap(i0 + 1, j0 + 1, R, ii, jj);
-  t.off[3] = jj * R + ii;
+  // oct_wrap of the four taps, axis by axis: a column outside mirrors the row and the other
+  // way round, and both are clamped
+  const int i1 = i0 + 1, j1 = j0 + 1, m = R - 1;
+  const int ci0 = max(i0, 0), ci1 = min(i1, m), cj0 = max(j0, 0), cj1 = min(j1, m);
+  const bool oi0 = i0 < 0, oi1 = i1 > m, oj0 = j0 < 0, oj1 = j1 > m;
+  const int ri0 = m - ci0, ri1 = m - ci1, rj0 = m - cj0, rj1 = m - cj1;
+  t.off[0] = (oi0 ? rj0 : cj0) * R + (oj0 ? ri0 : ci0);
+  t.off[1] = (oi1 ? rj0 : cj0) * R + (oj0 ? ri1 : ci1);
+  t.off[2] = (oi0 ? rj1 : cj1) * R + (oj1 ? ri0 : ci0);
+  t.off[3] = (oi1 ? rj1 : cj1) * R + (oj1 ? ri1 : ci1);
   // weights in FP64: 1 - fx cancels when fx is close to 1
   t.w[0] = (float)((1.0 - fx) * (1.0 - fy));
   t.w[1] = (float)(fx * (1.0 - fy));
@@ -235,39 +216,7 @@ struct EnvTaps {
   int vi, vj;    // corner tap before the wrap and the clamp, plus 2 (>= 0)
 };
 
-__device__ __forceinline__ EnvTaps env_taps(v3 w, int H, int W, float u_scale, float v_scale) {
-  const float theta = atan2f(sqrtf(w.x * w.x + w.y * w.y), w.z);
-  const float phi = atan2f(w.y, w.x);
-  // u = (phi + pi) W / (2 pi) = phi * W/(2pi) + W/2, one rounding
-  // clamped to [-0.5, W-0.5] x [-0.5, H-0.5] (NaN included) so every tap is in range
-  const float cu = fminf(fmaxf(fmaf(phi, u_scale, 0.5f * (float)W) - 0.5f, -0.5f),
-                         (float)W - 0.5f);
-  const float cv = fminf(fmaxf(theta * v_scale - 0.5f, -0.5f), (float)H - 0.5f);
-  const float i0f = floorf(cu), j0f = floorf(cv);
-  const float fx = cu - i0f, fy = cv - j0f;
-  int i0 = (int)i0f, j0 = (int)j0f;
-  const int vi = i0 + 2, vj = j0 + 2;
-  int i1 = i0 + 1, j1 = j0 + 1;
-  i0 = i0 < 0 ? i0 + W : (i0 >= W ? i0 - W : i0);
-  i1 = i1 < 0 ? i1 + W : (i1 >= W ? i1 - W : i1);
-  j0 = j0 < 0 ? 0 : (j0 > H - 1 ? H - 1 : j0);
-  j1 = j1 < 0 ? 0 : (j1 > H - 1 ? H - 1 : j1);
-  EnvTaps t;
-  t.vi = vi;
-  t.vj = vj;
-  t.off[0] = j0 * W + i0;
-  t.off[1] = j0 * W + i1;
-  t.off[2] = j1 * W + i0;
-  t.off[3] = j1 * W + i1;
-  t.w[0] = (1.0f - fx) * (1.0f - fy);
-  t.w[1] = fx * (1.0f - fy);
-  t.w[2] = (1.0f - fx) * fy;
-  t.w[3] = fx * fy;
-  return t;
-}
-
-// Accurate variant. The texel is chosen from the FP32 angles; the fraction inside it is the
-// FP64 angle between the direction and the texel's reference direction (the direction
+// The texel is chosen from FP32 angles; the fraction inside it is the FP64 angle between the direction and the texel's reference direction (the direction
 // at cu = i exactly, from a per-call table), through a small-angle arctangent series.
 // Both angles then carry ~1e-16 instead of ~1e-7 error, so bilinear weights (and the
 // gradients they scatter) are exact to FP32 rounding even when a weight is small.
@@ -307,25 +256,44 @@ __device__ __forceinline__ double angle_from(double c, double s, double x, doubl
   // small angles only (dt > 0), the rest (texels wider than a right angle, W < 8 or H < 4)
   // goes through the full arctangent
   const double cr = c * y - s * x, dt = c * x + s * y;
-  const double z = cr / dt;
+  const double z = cr * rcp64(dt);
   return (dt > 0.0 && fabs(z) <= 0.2) ? small_atan(z) : wide_atan2(cr, dt);
+}
+
+// atan2 within 3e-6, for the choice of a texel only (the widest map has texels of 1e-4, and
+// the fraction inside the texel corrects a choice that is off by one). The polynomial in
+// min/max is an equal-error fit of atan(t)/t in t^2 on [0, 1], 1.7e-6.
+__device__ __forceinline__ float atan2_texel(float y, float x) {
+  const float ax = fabsf(x), ay = fabsf(y);
+  const float t = fminf(ax, ay) * __builtin_amdgcn_rcpf(fmaxf(fmaxf(ax, ay), 1e-37f));
+  const float s = t * t;
+  float p = fmaf(s, -0.01171912f, 0.05264731f);
+  p = fmaf(s, p, -0.11642644f);
+  p = fmaf(s, p, 0.19354036f);
+  p = fmaf(s, p, -0.33262283f);
+  p = fmaf(s, p, 0.99997723f) * t;
+  p = ay > ax ? 1.57079633f - p : p;
+  p = x < 0.0f ? 3.14159265f - p : p;
+  return copysignf(p, y);
 }
 
 __device__ __forceinline__ EnvTaps env_taps64(const double w[3], int H, int W, float u_scale,
                                               float v_scale, const double2* col_ref,
                                               const double2* row_ref) {
   const float xf = (float)w[0], yf = (float)w[1], zf = (float)w[2];
-  const float rhof = sqrtf(xf * xf + yf * yf);
-  const float phif = atan2f(yf, xf), thetaf = atan2f(rhof, zf);
+  // sin(theta): the estimate 1 / sqrt(rho^2) and one Newton step to FP64 accuracy (2^-45)
+  const double rho2 = fma(w[0], w[0], w[1] * w[1]);
+  const float rho2f = (float)rho2;
+  const float rsf = rho2f > 1e-36f ? __builtin_amdgcn_rsqf(rho2f) : 0.0f;
+  const double rho0 = rho2 * (double)rsf;
+  const double rho = fma(0.5 * (double)rsf, fma(-rho0, rho0, rho2), rho0);
+  const float phif = atan2_texel(yf, xf), thetaf = atan2_texel((float)rho, zf);
   float cuf = fminf(fmaxf(fmaf(phif, u_scale, 0.5f * (float)W) - 0.5f, -0.5f), (float)W - 0.5f);
   float cvf = fminf(fmaxf(thetaf * v_scale - 0.5f, -0.5f), (float)H - 0.5f);
   int i0 = (int)floorf(cuf), j0 = (int)floorf(cvf);   // i0 in [-1, W-1], j0 in [-1, H-1]
   // exact fractions relative to the reference directions of i0 and j0
   const double2 cr = col_ref[i0 + 1];
   double fx = angle_from(cr.x, cr.y, w[0], w[1]) * ((double)W / (2.0 * 3.14159265358979323846));
-  double rho2 = w[0] * w[0] + w[1] * w[1];
-  double rho = (double)rhof;
-  rho = rho > 0.0 ? 0.5 * (rho + rho2 / rho) : 0.0;     // one Newton step to FP64 accuracy
   const double2 rr = row_ref[j0 + 1];
   // angle from theta_ref to theta in the (z, rho) plane, where the direction sits at angle
   // theta from +z and the reference at theta_ref = (cos, sin)
@@ -369,6 +337,7 @@ struct Material {
   float NoV;     // clamped n.v
   float one_m_k; // 1 - k
   float g1v;     // Smith G1(NoV)
+  float vis;     // alpha^2 G1(NoV) / (4 pi NoV): the factors of spec that no sample changes
 };
 
 // NoV is formed in FP64 by the caller: for grazing views n.v is a small difference of
@@ -385,6 +354,7 @@ __device__ __forceinline__ Material make_material(float NoV_clamped, v3 albedo, 
   M.one_m_k = 1.0f - M.k;
   M.NoV = NoV_clamped;
   M.g1v = M.NoV / (M.NoV * M.one_m_k + M.k);
+  M.vis = M.a2 * kInvPi * M.g1v / (4.0f * M.NoV);
   return M;
 }
 
@@ -402,7 +372,7 @@ __device__ __forceinline__ HalfGeom half_geom(const double n[3], const double v[
   const double hh = fma(h0, h0, fma(h1, h1, h2 * h2));
   const double c = fma(n[0], h0, fma(n[1], h1, n[2] * h2));
   const double vh = fma(v[0], h0, fma(v[1], h1, v[2] * h2));
-  const double NoH2 = c * c / hh;
+  const double NoH2 = c * c * rcp64(hh);
   HalfGeom g;
   g.NoH2 = (float)NoH2;
   g.one_m = (float)(1.0 - NoH2);
@@ -411,8 +381,10 @@ __device__ __forceinline__ HalfGeom half_geom(const double n[3], const double v[
 }
 
 struct BrdfTerms {
-  float D, G1L, q, one_m, NoH2, x5;   // GGX pieces
-  float spec;                         // D * G / (4 NoV) (times cos cancels 1/NoL)
+  float iq;                 // 1 / q, q = NoH^2 (alpha^2 - 1) + 1: D = alpha^2 iq^2 / pi
+  float G1L, iL;            // Smith G1(NoL) = NoL iL
+  float one_m, NoH2, x5;
+  float spec;               // D * G / (4 NoV) (times cos cancels 1/NoL)
 };
 
 __device__ __forceinline__ BrdfTerms brdf_terms(const Material& M, const HalfGeom& hg,
@@ -420,13 +392,13 @@ __device__ __forceinline__ BrdfTerms brdf_terms(const Material& M, const HalfGeo
   BrdfTerms T;
   T.one_m = hg.one_m;
   T.NoH2 = hg.NoH2;
-  T.q = fmaf(M.a2, T.NoH2, T.one_m);       // = NoH^2 (alpha^2 - 1) + 1
-  T.D = M.a2 / (kPi * T.q * T.q);
-  T.G1L = NoL / (NoL * M.one_m_k + M.k);
+  T.iq = rcp32(fmaf(M.a2, T.NoH2, T.one_m));
+  T.iL = rcp32(fmaf(NoL, M.one_m_k, M.k));
+  T.G1L = NoL * T.iL;
   const float x = 1.0f - hg.VoH;
   const float x2 = x * x;
   T.x5 = x2 * x2 * x;
-  T.spec = T.D * T.G1L * M.g1v / (4.0f * M.NoV);
+  T.spec = (M.vis * T.iq) * T.iq * T.G1L;    // in this order: iq^2 alone may overflow
   return T;
 }
 
