@@ -644,6 +644,38 @@ __global__ __launch_bounds__(1024) void k_env_add(int32_t T, const uint64_t* til
   if (t < T && blockIdx.x > 0) prefix[t] += tile_off[blockIdx.x];
 }
 
+// floor(num / S) for num < 2^46 and S <= 4096, through FP64 (every product here is exact): the
+// quotient estimate is within one, and the remainder tells which way. An integer division of
+// 64 bits takes ~100 instructions.
+__device__ __forceinline__ uint64_t slice_div(uint64_t num, double S, double inv_S) {
+  const double n = (double)num;
+  double q = floor(n * inv_S);
+  const double r = fma(-q, S, n);
+  q += r >= S ? 1.0 : (r < 0.0 ? -1.0 : 0.0);
+  return (uint64_t)q;
+}
+
+// Sky draws: PPW points per wavefront, 64 / PPW lanes each. Draw j of every point comes from
+// the j-th slice of the same mass line, so neighbouring points that take the same draw look
+// at nearly the same texel of the sky and, there, at the same texels of the same probes:
+// the points of a wavefront are neighbouring lanes, lane = PPW (draw slot) + point, and a
+// gather reads a few cache lines where the draws of one point in neighbouring lanes read
+// one each.
+template <int PPW>
+__device__ __forceinline__ int64_t sky_slot(int lane) {
+  return (die_block() * kWavesPerBlock + wave_id_uniform()) * PPW + lane % PPW;
+}
+template <int PPW>
+__device__ __forceinline__ float sky_sum(float v) {      // over the lanes of a point
+  if constexpr (PPW == 1) {
+    return wave_sum(v);
+  } else {
+#pragma unroll
+    for (int o = PPW; o < 64; o <<= 1) v += __shfl_xor(v, o);
+    return v;
+  }
+}
+
 // 1 / pdf of an environment importance draw of texel mass m (total C, T texels) in the unit
 // direction w: Eq. 18's density (m / C) T / (4 pi), or with exact the draw's own density
 // (m / C) (T / 4) / s^3, s = |w_x| + |w_y| + |w_z| (the octahedral square's area element).
@@ -656,14 +688,15 @@ __device__ __forceinline__ float env_inv_pdf(const double w[3], uint32_t m, uint
   return (float)(12.566370614359172 * (double)C / ((double)m * (double)T));
 }
 
-// L lanes per point (64/L points per wavefront, in processing order; L = 64 for S > 32),
-// lane l of a point takes directions l, l+L, ...; the estimates of Eq. 15 and 16 share
-// every sample, and the ratio is formed after the lane-group sums.
-template <int KT, typename TexT, int L>
+// PPW points per wavefront in processing order (sky_slot); draw slot q of a point takes
+// directions q, q + 64 / PPW, ...; the estimates of Eq. 15 and 16 share every sample, and the
+// ratio is formed after the sums over the point's lanes.
+template <int KT, typename TexT, int PPW>
 __global__ __launch_bounds__(256) void k_shadow_ratio(ShadeArgs a, int32_t k) {
-  const int lane = threadIdx.x & 63, li = lane % L;
-  if ((die_block() * kWavesPerBlock + wave_id_uniform()) * (64 / L) >= a.n) return;
-  const int64_t slot = group_slot<L>(lane);
+  constexpr int L = 64 / PPW;
+  const int lane = threadIdx.x & 63, li = lane / PPW;
+  if ((die_block() * kWavesPerBlock + wave_id_uniform()) * PPW >= a.n) return;
+  const int64_t slot = sky_slot<PPW>(lane);
   bool valid = slot < a.n;
   int64_t p = valid ? slot : 0;
   if (valid && a.order) {
@@ -693,6 +726,7 @@ __global__ __launch_bounds__(256) void k_shadow_ratio(ShadeArgs a, int32_t k) {
   const int32_t T = Re * Re;
   const uint64_t C = a.env_prefix ? a.env_prefix[T] : 0;
   const uint32_t sh = pcg_hash(a.seed);
+  const double inv_S = 1.0 / (double)a.S;
   const TexT* tex = reinterpret_cast<const TexT*>(a.tex);
   const size_t RR = (size_t)a.R * a.R;
   float num[3] = {0.0f, 0.0f, 0.0f}, den[3] = {0.0f, 0.0f, 0.0f};
@@ -707,7 +741,7 @@ __global__ __launch_bounds__(256) void k_shadow_ratio(ShadeArgs a, int32_t k) {
     } else {
       // the j-th of S slices of the mass line, then the texel whose stretch holds x
       const uint64_t r = hash24(sh, (uint32_t)p, (uint32_t)j, 0);
-      const uint64_t x = ((uint64_t)j * C + ((r * C) >> 24)) / (uint64_t)a.S;
+      const uint64_t x = slice_div((uint64_t)j * C + ((r * C) >> 24), (double)a.S, inv_S);
       const int lo = env_pick(a.env_prefix, a.env_guide, T, C, x);
       const double xu = ((double)hash24(sh, (uint32_t)p, (uint32_t)j, 1) + 0.5) * 0x1p-24;
       const double xv = ((double)hash24(sh, (uint32_t)p, (uint32_t)j, 2) + 0.5) * 0x1p-24;
@@ -751,8 +785,8 @@ __global__ __launch_bounds__(256) void k_shadow_ratio(ShadeArgs a, int32_t k) {
   float rn[3], rd[3];
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
-    rn[c] = group_sum<L>(num[c]);
-    rd[c] = group_sum<L>(den[c]);
+    rn[c] = sky_sum<PPW>(num[c]);
+    rd[c] = sky_sum<PPW>(den[c]);
   }
   if (valid && li == 0) {
 #pragma unroll
@@ -769,14 +803,15 @@ __global__ __launch_bounds__(256) void k_shadow_ratio(ShadeArgs a, int32_t k) {
 // are both estimated with the density of Eq. 18): the shading estimate of Eq. 6-9 with the
 // draws of the cast-shadow ratio's Eq. 18 sampler on an octahedral environment,
 // rgb = (1/S) sum_j f L_i cos+ / pdf_j with pdf_j = (m_t / C) R_e^2 / (4 pi), or the draw's
-// exact density (env_inv_pdf); draws below the horizon add nothing. L lanes per point (64/L points per wavefront), lane l of a point
-// taking draws l, l + L, ...
+// exact density (env_inv_pdf); draws below the horizon add nothing. PPW points per
+// wavefront (sky_slot), draw slot q of a point taking draws q, q + 64 / PPW, ...
 // ------------------------------------------------------------------------------------------
-template <int KT, typename TexT, int L>
+template <int KT, typename TexT, int PPW>
 __global__ __launch_bounds__(256) void k_shade_envis(ShadeArgs a, int32_t k) {
-  const int lane = threadIdx.x & 63, li = lane % L;
-  if ((die_block() * kWavesPerBlock + wave_id_uniform()) * (64 / L) >= a.n) return;
-  const int64_t slot = group_slot<L>(lane);
+  constexpr int L = 64 / PPW;
+  const int lane = threadIdx.x & 63, li = lane / PPW;
+  if ((die_block() * kWavesPerBlock + wave_id_uniform()) * PPW >= a.n) return;
+  const int64_t slot = sky_slot<PPW>(lane);
   PointState ps;
   const bool valid = slot < a.n && load_point<L == 64>(a, slot, ps);
   if (L == 64 && !valid) return;
@@ -787,11 +822,12 @@ __global__ __launch_bounds__(256) void k_shade_envis(ShadeArgs a, int32_t k) {
     const int32_t Re = a.env_res, T = Re * Re;
     const uint64_t C = a.env_prefix[T];
     const uint32_t sh = pcg_hash(a.seed), pi = (uint32_t)ps.p;
+    const double inv_S = 1.0 / (double)a.S;
     const float al[3] = {ps.M.a.x, ps.M.a.y, ps.M.a.z};
     for (int j = li; j < a.S; j += L) {
       // the j-th of S slices of the mass line, then the texel whose stretch holds x
       const uint64_t r = hash24(sh, pi, (uint32_t)j, 0);
-      const uint64_t x = ((uint64_t)j * C + ((r * C) >> 24)) / (uint64_t)a.S;
+      const uint64_t x = slice_div((uint64_t)j * C + ((r * C) >> 24), (double)a.S, inv_S);
       const int lo = env_pick(a.env_prefix, a.env_guide, T, C, x);
       const double xu = ((double)hash24(sh, pi, (uint32_t)j, 1) + 0.5) * 0x1p-24;
       const double xv = ((double)hash24(sh, pi, (uint32_t)j, 2) + 0.5) * 0x1p-24;
@@ -815,7 +851,7 @@ __global__ __launch_bounds__(256) void k_shade_envis(ShadeArgs a, int32_t k) {
   const float scale = 1.0f / (float)a.S;
   float r3[3];
 #pragma unroll
-  for (int c = 0; c < 3; ++c) r3[c] = group_sum<L>(acc[c]) * scale;
+  for (int c = 0; c < 3; ++c) r3[c] = sky_sum<PPW>(acc[c]) * scale;
   if (valid && li == 0) {
     a.rgb[3 * ps.p] = r3[0];
     a.rgb[3 * ps.p + 1] = r3[1];
@@ -823,7 +859,7 @@ __global__ __launch_bounds__(256) void k_shade_envis(ShadeArgs a, int32_t k) {
   }
   if (a.irr) {
 #pragma unroll
-    for (int c = 0; c < 3; ++c) r3[c] = group_sum<L>(acc_e[c]) * scale;
+    for (int c = 0; c < 3; ++c) r3[c] = sky_sum<PPW>(acc_e[c]) * scale;
     if (valid && li == 0) {
       a.irr[3 * ps.p] = r3[0];
       a.irr[3 * ps.p + 1] = r3[1];
@@ -1889,21 +1925,35 @@ hipError_t launch_env_cdf(const float* env, int32_t T, uint32_t* mass, uint64_t*
   return hipGetLastError();
 }
 
-template <int KT, int L>
+// Points per wavefront of the sky estimates. Up to 32 draws, a wavefront of one point would
+// leave lanes idle: four points (500k ground points, S = 16, exact density: 0.48 ms against
+// 0.85 with one and 0.46-0.47 with 16 or 64; 60k relit points, S = 16: 0.098 against 0.166
+// with one and 0.112 with 16; 200k: 0.208, with 16 0.188).
+// Above that four points gain cache lines but lose wavefronts, and the estimate that reads
+// whole texels is better off alone: the shadow ratio takes four points from kSkyShared points
+// on (S = 64, one / four / 16 points: 500k 1.09 / 1.02 / 1.18 ms, 60k 0.232 / 0.228 / 0.279, 20k
+// 0.145 / 0.150 / 0.195), relighting never (200k points, S = 128: 0.72 / 0.87 / 0.87 ms).
+constexpr int64_t kSkyShared = 60000, kSkyMany = 131072;
+static int sky_points(int64_t n, int32_t S, bool whole_texels) {
+  if (whole_texels) return S > 32 ? 1 : (n >= kSkyMany ? 16 : 4);
+  return S > 32 && n < kSkyShared ? 1 : 4;
+}
+
+template <int KT, int PPW>
 static void launch_envis_l(const ShadeArgs& a, int32_t k, int32_t format, hipStream_t s) {
-  const dim3 grid = grid_for(a.n, L);
+  const dim3 grid = grid_for(a.n, 64 / PPW);
   if (format == SOP_TEXEL_F16)
-    hipLaunchKernelGGL((k_shade_envis<KT, uint2, L>), grid, dim3(256), 0, s, a, k);
+    hipLaunchKernelGGL((k_shade_envis<KT, uint2, PPW>), grid, dim3(256), 0, s, a, k);
   else
-    hipLaunchKernelGGL((k_shade_envis<KT, float4, L>), grid, dim3(256), 0, s, a, k);
+    hipLaunchKernelGGL((k_shade_envis<KT, float4, PPW>), grid, dim3(256), 0, s, a, k);
 }
 
 template <int KT>
 static void launch_envis_kt(const ShadeArgs& a, int32_t k, int32_t format, hipStream_t s) {
-  switch (lanes_for(a.S)) {
+  switch (sky_points(a.n, a.S, true)) {
     case 16: launch_envis_l<KT, 16>(a, k, format, s); break;
-    case 32: launch_envis_l<KT, 32>(a, k, format, s); break;
-    default: launch_envis_l<KT, 64>(a, k, format, s); break;
+    case 4: launch_envis_l<KT, 4>(a, k, format, s); break;
+    default: launch_envis_l<KT, 1>(a, k, format, s); break;
   }
 }
 
@@ -1918,22 +1968,19 @@ hipError_t launch_shade_envis(const ShadeArgs& a, int32_t k, int32_t format, hip
   return hipGetLastError();
 }
 
-template <int KT, int L>
+template <int KT, int PPW>
 static void launch_shadow_l(const ShadeArgs& a, int32_t k, int32_t format, hipStream_t s) {
-  const dim3 grid = grid_for(a.n, L);
+  const dim3 grid = grid_for(a.n, 64 / PPW);
   if (format == SOP_TEXEL_F16)
-    hipLaunchKernelGGL((k_shadow_ratio<KT, uint2, L>), grid, dim3(256), 0, s, a, k);
+    hipLaunchKernelGGL((k_shadow_ratio<KT, uint2, PPW>), grid, dim3(256), 0, s, a, k);
   else
-    hipLaunchKernelGGL((k_shadow_ratio<KT, float4, L>), grid, dim3(256), 0, s, a, k);
+    hipLaunchKernelGGL((k_shadow_ratio<KT, float4, PPW>), grid, dim3(256), 0, s, a, k);
 }
 
 template <int KT>
 static void launch_shadow_kt(const ShadeArgs& a, int32_t k, int32_t format, hipStream_t s) {
-  switch (lanes_for(a.S)) {
-    case 16: launch_shadow_l<KT, 16>(a, k, format, s); break;
-    case 32: launch_shadow_l<KT, 32>(a, k, format, s); break;
-    default: launch_shadow_l<KT, 64>(a, k, format, s); break;
-  }
+  if (sky_points(a.n, a.S, false) == 4) launch_shadow_l<KT, 4>(a, k, format, s);
+  else launch_shadow_l<KT, 1>(a, k, format, s);
 }
 
 hipError_t launch_shadow_ratio(const ShadeArgs& a, int32_t k, int32_t format, hipStream_t s) {
