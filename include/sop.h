@@ -477,7 +477,11 @@ sop_status sop_shadow_ratio(const sop_plan* plan, const sop_probe_maps* maps,
                             void* ws, size_t ws_bytes, sop_stream stream);
 
 /* Workspace bytes of sop_shadow_ratio (direction table, texel masses and their prefix sums,
- * and the neighbour search unless with_neighbors != 0). Returns 0 on an invalid argument. */
+ * and the neighbour search unless with_neighbors != 0). Returns 0 on an invalid argument.
+ * A workspace larger by count * (res + 2)^2 values of the maps' own type (4 or 2 bytes, of the
+ * plan's probe count and the maps' resolution; 256 bytes more for alignment) lets a call of
+ * many samples copy the maps' occlusion channel out before it reads it; the result is the
+ * same. */
 size_t sop_shadow_workspace_size(const sop_plan* plan, int64_t n_points, int32_t k,
                                  int32_t n_dirs, int32_t env_res, int32_t with_neighbors);
 

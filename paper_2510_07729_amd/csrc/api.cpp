@@ -230,7 +230,6 @@ struct EnvCdf {
   uint32_t* mass;
   uint64_t* prefix;
   uint64_t* tiles;
-  float* imax;
   int32_t* guide;
 };
 
@@ -239,7 +238,6 @@ EnvCdf carve_env_cdf(Bump& b, size_t T) {
   c.mass = b.take<uint32_t>(T);
   c.prefix = b.take<uint64_t>(T + 1);
   c.tiles = b.take<uint64_t>((T + 1023) / 1024 + 1);
-  c.imax = b.take<float>(1);
   c.guide = b.take<int32_t>((size_t)sopk::kEnvGuide + 1);
   return c;
 }
@@ -641,7 +639,7 @@ extern "C" sop_status sop_shade(const sop_plan* plan, const sop_probe_maps* maps
     a.env_prefix = cdf.prefix;
     a.env_guide = cdf.guide;
     SOP_HIP(sopk::launch_env_cdf(env->texels, env->width * env->height, cdf.mass, cdf.prefix,
-                                 cdf.tiles, cdf.imax, cdf.guide, s),
+                                 cdf.tiles, cdf.guide, s),
             "sop_shade");
     SOP_HIP(sopk::launch_shade_envis(a, kk, maps->format, s), "sop_shade");
   } else {
@@ -1369,7 +1367,6 @@ size_t shadow_ws(const sop_plan* plan, int64_t N, int32_t k, int32_t S, int32_t 
   (void)b.take<uint32_t>((size_t)Re * Re);
   (void)b.take<uint64_t>((size_t)Re * Re + 1);
   (void)b.take<uint64_t>(((size_t)Re * Re + 1023) / 1024);
-  (void)b.take<float>(1);
   (void)b.take<int32_t>((size_t)sopk::kEnvGuide + 1);
   if (!with_nb) {
     carve_nb(b, N, k);
@@ -1453,7 +1450,6 @@ extern "C" sop_status sop_shadow_ratio(const sop_plan* plan, const sop_probe_map
   uint32_t* mass = b.take<uint32_t>((size_t)T);
   uint64_t* prefix = b.take<uint64_t>((size_t)T + 1);
   uint64_t* tile_tmp = b.take<uint64_t>(((size_t)T + 1023) / 1024);
-  float* imax = b.take<float>(1);
   int32_t* guide = b.take<int32_t>((size_t)sopk::kEnvGuide + 1);
   if (opts->sampler == SOP_SHADOW_HAMMERSLEY) {
     a.dir_tab = tab;
@@ -1465,13 +1461,24 @@ extern "C" sop_status sop_shadow_ratio(const sop_plan* plan, const sop_probe_map
     a.env_mass = mass;
     a.env_prefix = prefix;
     a.env_guide = guide;
-    SOP_HIP(sopk::launch_env_cdf(env->texels, T, mass, prefix, tile_tmp, imax, guide, s),
+    SOP_HIP(sopk::launch_env_cdf(env->texels, T, mass, prefix, tile_tmp, guide, s),
             "sop_shadow_ratio");
   }
   int32_t kk;
   if ((st = resolve_nb(plan, pts, nb, opts->k, opts->radius, b, s, &a.order, &a.nb_idx,
                        &a.nb_w, &kk)) != SOP_OK)
     return st;
+  // with room left in the workspace, and enough samples to earn the pass over the maps, the
+  // occlusion channel is copied out first (every sample reads 4 K of its values)
+  const size_t texels = sopk::occ_map_texels(plan->P, maps->res);
+  const size_t bytes = texels * (maps->format == SOP_TEXEL_F16 ? 2 : 4);
+  if ((size_t)pts->count * (size_t)opts->n_dirs >= texels && b.used <= ws_bytes &&
+      ws_bytes - b.used >= bytes) {
+    void* occ = b.take<char>(bytes);
+    SOP_HIP(sopk::launch_pack_occ(maps->texels, plan->P, maps->res, maps->format, occ, s),
+            "sop_shadow_ratio");
+    a.occ = occ;
+  }
   SOP_HIP(sopk::launch_shadow_ratio(a, kk, maps->format, s), "sop_shadow_ratio");
   return SOP_OK;
 }

@@ -543,9 +543,11 @@ __device__ __forceinline__ float env_intensity(const float* e) {
 }
 
 // Texel masses m_t = 1 + floor(I_t * (2^14 / I_max)) (one IEEE division, one product; all 1
-// when I_max = 0) and their exclusive prefix sums, prefix[T] = the total, in four coalesced
-// passes: the maximum (one workgroup), masses and a scan inside tiles of 1024 texels, a
-// scan of the tile totals (one workgroup; T <= 2^20), and the tile offsets added.
+// when I_max = 0) and their exclusive prefix sums, prefix[T] = the total, in three coalesced
+// passes over tiles of 1024 texels (T <= 2^20, so a workgroup can go over all tiles' values):
+// the tiles' maxima, masses and a scan inside each tile, and the sums of the tiles before
+// added. The call makes them for every sky it is given: 65,536 texels and the guide take
+// 19 us (38 us with the maximum and the tile offsets in workgroups of their own).
 constexpr int kCdfTile = 1024;
 
 // cell width (log2) of the guide of a mass line of total C: 2^16 cells at most
@@ -583,18 +585,24 @@ __global__ __launch_bounds__(256) void k_env_guide(const uint64_t* __restrict__ 
   guide[g] = lo;
 }
 
-__global__ __launch_bounds__(1024) void k_env_max(const float* env, int32_t T, float* imax) {
-  __shared__ float smax[1024];
+// the largest v over a 1024-thread workgroup, to every thread
+__device__ __forceinline__ float block_max_1024(float v, float* sh) {
   const int tid = threadIdx.x;
-  float m = 0.0f;
-  for (int t = tid; t < T; t += 1024) m = fmaxf(m, env_intensity(env + 3 * (size_t)t));
-  smax[tid] = m;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
+  if ((tid & 63) == 0) sh[tid >> 6] = v;
   __syncthreads();
-  for (int o = 512; o > 0; o >>= 1) {
-    if (tid < o) smax[tid] = fmaxf(smax[tid], smax[tid + o]);
-    __syncthreads();
-  }
-  if (tid == 0) *imax = smax[0];
+  v = sh[tid & 15];
+#pragma unroll
+  for (int o = 8; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
+  return v;
+}
+
+__global__ __launch_bounds__(1024) void k_env_max(const float* env, int32_t T, float* tile_max) {
+  __shared__ float sh[16];
+  const int t = blockIdx.x * kCdfTile + threadIdx.x;
+  const float m = block_max_1024(t < T ? env_intensity(env + 3 * (size_t)t) : 0.0f, sh);
+  if (threadIdx.x == 0) tile_max[blockIdx.x] = m;
 }
 
 // inclusive scan of one value per thread over a 1024-thread workgroup (Hillis-Steele)
@@ -612,10 +620,12 @@ __device__ __forceinline__ uint64_t block_scan_1024(uint64_t v, uint64_t* sh) {
 }
 
 __global__ __launch_bounds__(1024) void k_env_tiles(const float* env, int32_t T,
-                                                    const float* imax, uint32_t* mass,
+                                                    const float* tile_max, uint32_t* mass,
                                                     uint64_t* prefix, uint64_t* tile_sum) {
   __shared__ uint64_t sh[1024];
-  const float im = *imax;
+  __shared__ float shm[16];
+  const float im =
+      block_max_1024(threadIdx.x < gridDim.x ? tile_max[threadIdx.x] : 0.0f, shm);
   const float f = im > 0.0f ? __fdiv_rn(16384.0f, im) : 0.0f;
   const int t = blockIdx.x * kCdfTile + threadIdx.x;
   uint32_t m = 0;
@@ -628,20 +638,28 @@ __global__ __launch_bounds__(1024) void k_env_tiles(const float* env, int32_t T,
   if (threadIdx.x == 1023) tile_sum[blockIdx.x] = inc;
 }
 
-__global__ __launch_bounds__(1024) void k_env_tile_scan(int32_t ntiles, uint64_t* tile_sum,
-                                                        uint64_t* prefix, int32_t T) {
-  __shared__ uint64_t sh[1024];
-  const int b = threadIdx.x;
-  const uint64_t v = b < ntiles ? tile_sum[b] : 0;
-  const uint64_t inc = block_scan_1024(v, sh);
-  if (b < ntiles) tile_sum[b] = inc - v;           // offset of tile b
-  if (b == 1023) prefix[T] = inc;
+__device__ __forceinline__ uint64_t shfl_u64(uint64_t v, int src, int width) {
+  const uint32_t lo = __shfl((uint32_t)v, src, width), hi = __shfl((uint32_t)(v >> 32), src, width);
+  return ((uint64_t)hi << 32) | lo;
 }
 
-__global__ __launch_bounds__(1024) void k_env_add(int32_t T, const uint64_t* tile_off,
+// prefix[t] += the sums of the tiles before t's (each workgroup adds them up itself); the last
+// tile's workgroup also writes the total
+__global__ __launch_bounds__(1024) void k_env_add(int32_t T, const uint64_t* tile_sum,
                                                   uint64_t* prefix) {
-  const int t = blockIdx.x * kCdfTile + threadIdx.x;
-  if (t < T && blockIdx.x > 0) prefix[t] += tile_off[blockIdx.x];
+  __shared__ uint64_t sh[16];
+  const int tid = threadIdx.x, b = blockIdx.x;
+  uint64_t v = tid < b ? tile_sum[tid] : 0;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += shfl_u64(v, (tid & 63) ^ o, 64);
+  if ((tid & 63) == 0) sh[tid >> 6] = v;
+  __syncthreads();
+  uint64_t off = 0;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) off += sh[i];
+  const int t = b * kCdfTile + tid;
+  if (t < T && b > 0) prefix[t] += off;
+  if (b == (int)gridDim.x - 1 && tid == 0) prefix[T] = off + tile_sum[b];
 }
 
 // floor(num / S) for num < 2^46 and S <= 4096, through FP64 (every product here is exact): the
@@ -688,10 +706,42 @@ __device__ __forceinline__ float env_inv_pdf(const double w[3], uint32_t m, uint
   return (float)(12.566370614359172 * (double)C / ((double)m * (double)T));
 }
 
+// The occlusion maps of launch_pack_occ: one thread per value.
+template <typename TexT, typename OccT>
+__global__ __launch_bounds__(256) void k_pack_occ(const TexT* tex, int32_t R, int64_t n, OccT* occ) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  const int side = R + 2;
+  const int64_t p = i / (side * side);
+  const int v = (int)(i - p * (side * side)), row = v / side, col = v - row * side;
+  int ii, jj;
+  oct_wrap(col - 1, row - 1, R, ii, jj);
+  occ[i] = reinterpret_cast<const OccT*>(tex)[4 * (p * R * R + jj * R + ii) + 3];
+}
+
+// two adjacent values of an occlusion map (4-byte or 2-byte aligned)
+__device__ __forceinline__ float2 load_pair(const float* o) {
+  float2 v;
+  __builtin_memcpy(&v, o, sizeof(v));
+  return v;
+}
+__device__ __forceinline__ float2 load_pair(const __half* o) {
+  __half2 v;
+  __builtin_memcpy(&v, o, sizeof(v));
+  return __half22float2(v);
+}
+
 // PPW points per wavefront in processing order (sky_slot); draw slot q of a point takes
 // directions q, q + 64 / PPW, ...; the estimates of Eq. 15 and 16 share every sample, and the
-// ratio is formed after the sums over the point's lanes.
-template <int KT, typename TexT, int PPW>
+// ratio is formed after the sums over the point's lanes. Bound by the number of its gathers
+// (the texture unit takes 16 cycles for 64 lanes however little each reads), 32 of ~42 of
+// which are the occlusions of 8 probes: from the occlusion maps (OCC) they are 16 of twice the
+// width. 500k points, S = 64, exact density: 0.92 -> 0.64 ms, and
+// 10 us for the maps.
+template <typename TexT> struct OccOf;
+template <> struct OccOf<float4> { using T = float; };
+template <> struct OccOf<uint2> { using T = __half; };
+template <int KT, typename TexT, int PPW, bool OCC>
 __global__ __launch_bounds__(256) void k_shadow_ratio(ShadeArgs a, int32_t k) {
   constexpr int L = 64 / PPW;
   const int lane = threadIdx.x & 63, li = lane / PPW;
@@ -767,13 +817,25 @@ __global__ __launch_bounds__(256) void k_shadow_ratio(ShadeArgs a, int32_t k) {
       const int32_t id = nb.id(s2, a, p, k);
       if (id < 0) continue;
       const float wk = nb.wt(s2, a, p, k);
-      const TexT* Tp = tex + (size_t)id * RR;
-      // only the occlusion channel is read (a quarter of each texel)
-      float q[4];
+      if constexpr (OCC) {
+        using OccT = typename OccOf<TexT>::T;
+        const int side = a.R + 2;
+        const OccT* o = reinterpret_cast<const OccT*>(a.occ) + (size_t)id * (side * side) +
+                        (tt.j0 + 1) * side + tt.i0 + 1;
+        const float2 q0 = load_pair(o), q1 = load_pair(o + side);
+        O += wk * tt.w[0] * q0.x;
+        O += wk * tt.w[1] * q0.y;
+        O += wk * tt.w[2] * q1.x;
+        O += wk * tt.w[3] * q1.y;
+      } else {
+        const TexT* Tp = tex + (size_t)id * RR;
+        // only the occlusion channel is read (a quarter of each texel)
+        float q[4];
 #pragma unroll
-      for (int t = 0; t < 4; ++t) q[t] = load_occlusion(Tp, (size_t)tt.off[t]);
+        for (int t = 0; t < 4; ++t) q[t] = load_occlusion(Tp, (size_t)tt.off[t]);
 #pragma unroll
-      for (int t = 0; t < 4; ++t) O += wk * tt.w[t] * q[t];
+        for (int t = 0; t < 4; ++t) O += wk * tt.w[t] * q[t];
+      }
     }
     const float cw = ct * wt;
 #pragma unroll
@@ -898,10 +960,6 @@ __device__ __forceinline__ double cell_point(double xu, double xv, int b, double
 __device__ __forceinline__ uint64_t shfl_up_u64(uint64_t v, int d, int width) {
   const uint32_t lo = __shfl_up((uint32_t)v, d, width);
   const uint32_t hi = __shfl_up((uint32_t)(v >> 32), d, width);
-  return ((uint64_t)hi << 32) | lo;
-}
-__device__ __forceinline__ uint64_t shfl_u64(uint64_t v, int src, int width) {
-  const uint32_t lo = __shfl((uint32_t)v, src, width), hi = __shfl((uint32_t)(v >> 32), src, width);
   return ((uint64_t)hi << 32) | lo;
 }
 
@@ -1911,14 +1969,14 @@ hipError_t launch_shade_traced(const ShadeArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_env_cdf(const float* env, int32_t T, uint32_t* mass, uint64_t* prefix,
-                          uint64_t* tile_tmp, float* imax, int32_t* guide, hipStream_t s) {
-  if (T < 1 || T > (1 << 20) || !env || !mass || !prefix || !tile_tmp || !imax || !guide)
+                          uint64_t* tile_tmp, int32_t* guide, hipStream_t s) {
+  if (T < 1 || T > (1 << 20) || !env || !mass || !prefix || !tile_tmp || !guide)
     return hipErrorInvalidValue;
   const int ntiles = (T + kCdfTile - 1) / kCdfTile;
-  hipLaunchKernelGGL(k_env_max, dim3(1), dim3(1024), 0, s, env, T, imax);
-  hipLaunchKernelGGL(k_env_tiles, dim3(ntiles), dim3(1024), 0, s, env, T, imax, mass, prefix,
+  float* tile_max = reinterpret_cast<float*>(guide);     // until the guide is written
+  hipLaunchKernelGGL(k_env_max, dim3(ntiles), dim3(1024), 0, s, env, T, tile_max);
+  hipLaunchKernelGGL(k_env_tiles, dim3(ntiles), dim3(1024), 0, s, env, T, tile_max, mass, prefix,
                      tile_tmp);
-  hipLaunchKernelGGL(k_env_tile_scan, dim3(1), dim3(1024), 0, s, ntiles, tile_tmp, prefix, T);
   hipLaunchKernelGGL(k_env_add, dim3(ntiles), dim3(1024), 0, s, T, tile_tmp, prefix);
   hipLaunchKernelGGL(k_env_guide, dim3((kEnvGuide + 1 + 255) / 256), dim3(256), 0, s, prefix, T,
                      guide);
@@ -1926,17 +1984,22 @@ hipError_t launch_env_cdf(const float* env, int32_t T, uint32_t* mass, uint64_t*
 }
 
 // Points per wavefront of the sky estimates. Up to 32 draws, a wavefront of one point would
-// leave lanes idle: four points (500k ground points, S = 16, exact density: 0.48 ms against
-// 0.85 with one and 0.46-0.47 with 16 or 64; 60k relit points, S = 16: 0.098 against 0.166
-// with one and 0.112 with 16; 200k: 0.208, with 16 0.188).
+// leave lanes idle: four points (60k relit points, S = 16: 0.098 ms against 0.166 with one and
+// 0.112 with 16; 60k ground points, S = 16, exact density: 0.15 against 0.20 and 0.15).
 // Above that four points gain cache lines but lose wavefronts, and the estimate that reads
 // whole texels is better off alone: the shadow ratio takes four points from kSkyShared points
-// on (S = 64, one / four / 16 points: 500k 1.09 / 1.02 / 1.18 ms, 60k 0.232 / 0.228 / 0.279, 20k
-// 0.145 / 0.150 / 0.195), relighting never (200k points, S = 128: 0.72 / 0.87 / 0.87 ms).
+// on (S = 64, one / four / 16 points: 60k 0.184 / 0.188 / 0.184 ms, 150k 0.329 / 0.321 / 0.318; from
+// the maps themselves 500k 1.09 / 1.02 / 1.18), relighting does not (200k points, S = 128:
+// 0.72 / 0.87 / 0.87). Sixteen points pay in large calls whose lanes read little: relighting of
+// few draws (200k points, S = 16, four / 16: 0.208 / 0.188) and the ratio from occlusion maps
+// (500k, S = 16, four / 16 / 64: 0.404 / 0.345 / 0.337; S = 64: 0.795 / 0.715 / 0.732).
 constexpr int64_t kSkyShared = 60000, kSkyMany = 131072;
-static int sky_points(int64_t n, int32_t S, bool whole_texels) {
-  if (whole_texels) return S > 32 ? 1 : (n >= kSkyMany ? 16 : 4);
-  return S > 32 && n < kSkyShared ? 1 : 4;
+static int sky_points_relit(const ShadeArgs& a) {
+  return a.S > 32 ? 1 : (a.n >= kSkyMany ? 16 : 4);
+}
+static int sky_points_shadow(const ShadeArgs& a) {
+  if (a.occ && a.n >= kSkyMany) return 16;
+  return a.S > 32 && a.n < kSkyShared ? 1 : 4;
 }
 
 template <int KT, int PPW>
@@ -1950,7 +2013,7 @@ static void launch_envis_l(const ShadeArgs& a, int32_t k, int32_t format, hipStr
 
 template <int KT>
 static void launch_envis_kt(const ShadeArgs& a, int32_t k, int32_t format, hipStream_t s) {
-  switch (sky_points(a.n, a.S, true)) {
+  switch (sky_points_relit(a)) {
     case 16: launch_envis_l<KT, 16>(a, k, format, s); break;
     case 4: launch_envis_l<KT, 4>(a, k, format, s); break;
     default: launch_envis_l<KT, 1>(a, k, format, s); break;
@@ -1968,19 +2031,43 @@ hipError_t launch_shade_envis(const ShadeArgs& a, int32_t k, int32_t format, hip
   return hipGetLastError();
 }
 
-template <int KT, int PPW>
+template <int KT, int PPW, bool OCC>
 static void launch_shadow_l(const ShadeArgs& a, int32_t k, int32_t format, hipStream_t s) {
   const dim3 grid = grid_for(a.n, 64 / PPW);
   if (format == SOP_TEXEL_F16)
-    hipLaunchKernelGGL((k_shadow_ratio<KT, uint2, PPW>), grid, dim3(256), 0, s, a, k);
+    hipLaunchKernelGGL((k_shadow_ratio<KT, uint2, PPW, OCC>), grid, dim3(256), 0, s, a, k);
   else
-    hipLaunchKernelGGL((k_shadow_ratio<KT, float4, PPW>), grid, dim3(256), 0, s, a, k);
+    hipLaunchKernelGGL((k_shadow_ratio<KT, float4, PPW, OCC>), grid, dim3(256), 0, s, a, k);
 }
 
 template <int KT>
 static void launch_shadow_kt(const ShadeArgs& a, int32_t k, int32_t format, hipStream_t s) {
-  if (sky_points(a.n, a.S, false) == 4) launch_shadow_l<KT, 4>(a, k, format, s);
-  else launch_shadow_l<KT, 1>(a, k, format, s);
+  const int points = sky_points_shadow(a);
+  if (a.occ) {
+    if (points == 16) launch_shadow_l<KT, 16, true>(a, k, format, s);
+    else if (points == 4) launch_shadow_l<KT, 4, true>(a, k, format, s);
+    else launch_shadow_l<KT, 1, true>(a, k, format, s);
+  } else {
+    if (points == 4) launch_shadow_l<KT, 4, false>(a, k, format, s);
+    else launch_shadow_l<KT, 1, false>(a, k, format, s);
+  }
+}
+
+hipError_t launch_pack_occ(const void* texels, int32_t P, int32_t R, int32_t format, void* occ,
+                           hipStream_t s) {
+  const int64_t n = (int64_t)occ_map_texels(P, R);
+  if (n == 0) return hipSuccess;
+  if (!texels || !occ) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)((n + 255) / 256));
+  if (format == SOP_TEXEL_F16)
+    hipLaunchKernelGGL((k_pack_occ<uint2, uint16_t>), grid, dim3(256), 0, s,
+                       reinterpret_cast<const uint2*>(texels), R, n,
+                       reinterpret_cast<uint16_t*>(occ));
+  else
+    hipLaunchKernelGGL((k_pack_occ<float4, float>), grid, dim3(256), 0, s,
+                       reinterpret_cast<const float4*>(texels), R, n,
+                       reinterpret_cast<float*>(occ));
+  return hipGetLastError();
 }
 
 hipError_t launch_shadow_ratio(const ShadeArgs& a, int32_t k, int32_t format, hipStream_t s) {

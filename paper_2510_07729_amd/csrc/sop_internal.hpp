@@ -93,6 +93,7 @@ struct ShadeArgs {
   const uint64_t* env_prefix;  // [Re*Re + 1], env_prefix[Re*Re] = total mass
   const int32_t* env_guide;    // [kEnvGuide + 1] guide of the mass line (launch_env_cdf)
   int32_t env_res;
+  const void* occ;          // the maps' occlusion copied out (launch_pack_occ), or NULL
   int32_t shadow_sampler;   // 0 Hammersley, 1 environment importance sampling
   int32_t env_pdf_exact;    // importance draws weighted by their exact density (else Eq. 18's)
   // learned proposal sampler / training targets
@@ -186,16 +187,22 @@ hipError_t launch_env_blk_finish(const float* blk, int32_t bw, int32_t bh, int32
 hipError_t launch_shade_prop(const ShadeArgs& a, int32_t k, int32_t format, hipStream_t s);
 hipError_t launch_dump_integrand(const ShadeArgs& a, int32_t k, int32_t format, hipStream_t s);
 // cast-shadow ratio: texel masses and prefix of an octahedral environment [T <= 2^20
-// texels]; tile_tmp holds ceil(T/1024) values, imax one
+// texels]; tile_tmp holds ceil(T/1024) values
 // The sampler's texel for a point x of the mass line is the largest t with prefix[t] <= x.
 // guide[g] is that texel for x = g << shift (shift = max(0, bit length of the total - 16),
 // so g < 2^16 + 1 cells cover the line): the texel of any x in cell g lies in
 // [guide[g], guide[g + 1]], a few texels instead of the whole map.
 constexpr int kEnvGuide = 65536;
 hipError_t launch_env_cdf(const float* env, int32_t T, uint32_t* mass, uint64_t* prefix,
-                          uint64_t* tile_tmp, float* imax, int32_t* guide, hipStream_t s);
+                          uint64_t* tile_tmp, int32_t* guide, hipStream_t s);
 // relighting with environment importance sampling (a.env octahedral, a.env_mass/prefix)
 hipError_t launch_shade_envis(const ShadeArgs& a, int32_t k, int32_t format, hipStream_t s);
+// Occlusion maps: channel 3 of every map with a border of one texel, (R + 2)^2 values of the
+// maps' own type, where the border holds the values the mirror wrap finds there. A bilinear
+// footprint is then two adjacent values of two rows, whatever its place.
+inline size_t occ_map_texels(int32_t P, int32_t R) { return (size_t)P * (R + 2) * (R + 2); }
+hipError_t launch_pack_occ(const void* texels, int32_t P, int32_t R, int32_t format, void* occ,
+                           hipStream_t s);
 // ratio [n,3] in a.rgb (optional unshadowed estimate in a.irr)
 hipError_t launch_shadow_ratio(const ShadeArgs& a, int32_t k, int32_t format, hipStream_t s);
 // traced shading: the estimate of launch_shade_fwd with a.traced for L_in and O

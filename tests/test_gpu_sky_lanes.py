@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("n,S", [(1, 1), (5, 33), (61, 32), (59_999, 40), (60_001, 40),
-                                 (1003, 16)])
+                                 (1003, 16), (131_100, 2), (131_100, 34)])
 @pytest.mark.parametrize("sampler", [0, 2])
 def test_shadow_ratio(n, S, sampler):
     from paper_2510_07729_amd import sop
@@ -25,6 +25,15 @@ def test_shadow_ratio(n, S, sampler):
     rows = np.random.default_rng(n).choice(n, min(n, 500), replace=False)
     idx, w = oracle.knn(sc.probe_pos, sc.bounds_lo, sc.bounds_hi, sc.pos[rows], sc.normal[rows],
                         4)
+    # without room for the occlusion maps the call reads the texels themselves
+    ws = sop.workspace(plan._lib.sop_shadow_workspace_size(plan.handle, n, 4, S, 16, 0), "cuda")
+    plain = sop.sop_shadow_ratio(plan, dev(sc.texels), dev(sc.env), pts, S, k=4, seed=3,
+                                 sampler=sampler, ws=ws).cpu().numpy()
+    half = [sop.sop_shadow_ratio(plan, dev(sc.texels).half(), dev(sc.env), pts, S, k=4, seed=3,
+                                 sampler=sampler, ws=w).cpu().numpy() for w in (None, ws)]
+    # sums of S terms of one sign in another order, and their quotient
+    for a, b in ((out, plain), half):
+        assert np.all(np.abs(a - b) <= 2.0 ** -22 * (S + 8) * np.abs(b))
     ref = oracle.shadow_ratio(sc.normal[rows], sc.texels, idx, w, sc.env, S, seed=3,
                               sampler=sampler, ids=rows)["ratio"]
     assert parity_err(out[rows], ref).max() <= TOL
