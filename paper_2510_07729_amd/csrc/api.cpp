@@ -1004,7 +1004,6 @@ struct sop_bake_plan {
   uint64_t* cellmask = nullptr;   // [G][kCellMaskWords] acceptance bits of the count pass
   int32_t* counts = nullptr;
   int32_t* cell_start = nullptr;
-  int32_t* cursor = nullptr;
   int32_t* entries = nullptr;
   int32_t capacity = 0;
   int32_t* scan_tmp = nullptr;
@@ -1013,12 +1012,12 @@ struct sop_bake_plan {
   size_t ncell = 0;
 
   void release() {
-    void* ptrs[] = {gdata, aabb, cellmask, counts, cell_start, cursor, entries, scan_tmp, misc};
+    void* ptrs[] = {gdata, aabb, cellmask, counts, cell_start, entries, scan_tmp, misc};
     for (void* p : ptrs)
       if (p) (void)hipFree(p);
     gdata = aabb = nullptr;
     cellmask = nullptr;
-    counts = cell_start = cursor = entries = scan_tmp = misc = nullptr;
+    counts = cell_start = entries = scan_tmp = misc = nullptr;
   }
 };
 
@@ -1055,7 +1054,6 @@ sop_bake_opts resolve_bake_opts(const sop_bake_opts* o) {
 
 hipError_t register_gaussians(sop_bake_plan* pl, hipStream_t s) {
   hipError_t e = sopk::launch_fill_i32(pl->counts, 0, pl->ncell, s);
-  if (e == hipSuccess) e = sopk::launch_fill_i32(pl->cursor, 0, pl->ncell, s);
   if (e == hipSuccess)
     e = sopk::launch_gauss_count(pl->grid, pl->aabb, pl->counts, pl->cellmask, pl->misc + 7, s);
   if (e == hipSuccess)
@@ -1158,7 +1156,6 @@ extern "C" sop_status sop_bake_plan_create(const sop_gaussians* g, const sop_bak
   const size_t C1 = pl->ncell > 0 ? pl->ncell : 1;
   alloc((void**)&pl->counts, C1 * sizeof(int32_t));
   alloc((void**)&pl->cell_start, (C1 + 1) * sizeof(int32_t));
-  alloc((void**)&pl->cursor, C1 * sizeof(int32_t));
   alloc((void**)&pl->scan_tmp, sopk::scan_tmp_elems(C1) * sizeof(int32_t));
   if (e != hipSuccess) return bail(SOP_ERR_OUT_OF_MEMORY, "bake grid allocation");
   G.cell_start = pl->cell_start;
@@ -1176,7 +1173,7 @@ extern "C" sop_status sop_bake_plan_create(const sop_gaussians* g, const sop_bak
   if (e != hipSuccess) return bail(SOP_ERR_OUT_OF_MEMORY, "bake entries allocation");
   G.entries = pl->entries;
   G.capacity = pl->capacity;
-  e = sopk::launch_gauss_fill(G, pl->aabb, pl->cellmask, pl->cell_start, pl->cursor,
+  e = sopk::launch_gauss_fill(G, pl->aabb, pl->cellmask, pl->cell_start, pl->counts,
                               pl->entries, pl->capacity, pl->misc + 7, s);
   if (e != hipSuccess) return bail(SOP_ERR_DEVICE, std::string("bake fill: ") + hipGetErrorString(e));
   *out = pl;
@@ -1201,7 +1198,7 @@ extern "C" sop_status sop_bake_plan_update(sop_bake_plan* plan, const sop_gaussi
   }
   SOP_HIP(register_gaussians(plan, s), "sop_bake_plan_update");
   SOP_HIP(sopk::launch_gauss_fill(plan->grid, plan->aabb, plan->cellmask, plan->cell_start,
-                                  plan->cursor, plan->entries, plan->capacity, plan->misc + 7,
+                                  plan->counts, plan->entries, plan->capacity, plan->misc + 7,
                                   s),
           "sop_bake_plan_update");
   return SOP_OK;

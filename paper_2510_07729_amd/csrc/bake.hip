@@ -4,13 +4,12 @@
 // Every Gaussian is turned into its whitening map M = S^-1 R^T (ray in Gaussian units) and
 // registered in the cells of a uniform grid that its cut-off ellipsoid (where
 // opacity * exp(-m^2/2) can reach alpha_min) overlaps: the cells of its axis-aligned box
-// that pass a separating-axis test along the ellipsoid's own axes and an exact test (the
-// minimum of the ellipsoid's quadratic form over the cell), all padded for FP32 rounding;
-// one wavefront registers one Gaussian.
-// Two lanes trace one texel's ray; a wavefront covers an 8x4 texel block of one probe so
-// that its rays stay coherent. The ray walks the grid cell by cell (3D DDA); a Gaussian is
-// composited in the cell whose t-window [t_enter, t_exit) holds its t*. Within a cell the
-// two lanes split the candidates. Each lane first screens its candidates in FP32 (t* in
+// that pass a separating-axis test along the ellipsoid's own axes and a test of the
+// minimum of the ellipsoid's quadratic form over the cell, all padded for FP32 rounding.
+// Two lanes trace one texel's ray (four or eight in calls of few rays); a wavefront covers a
+// block of one probe's texels so that its rays stay coherent. The ray walks the grid cell by
+// cell (3D DDA); a Gaussian is composited in the cell whose t-window [t_enter, t_exit) holds its t*. Within a cell the
+// lanes split the candidates. Each lane first screens its candidates in FP32 (t* in
 // the window and m^2 under the cut-off, both with margins far above the FP32 error) and
 // keeps the survivors in LDS, then runs the exact FP64 test on those only, so the FP64
 // work is done for about one candidate in six and by all lanes together. Accepted keys
@@ -143,85 +142,63 @@ __device__ __forceinline__ bool cell_overlaps(const BakeGrid& G, const float4* g
   return true;
 }
 
-// Whether the cut-off ellipsoid (padded like the box) meets cell (cx, cy, cz), exactly:
-// the minimum of q(x) = (x - mean)^T M^T M (x - mean) over the cell (enlarged by 1e-5) is at
-// most the padded cut-off. The minimiser of this convex quadratic over a box has each
-// coordinate either free (zero gradient) or at a bound, so the minimum is the smallest q
-// over the 26 patterns of fixed coordinates whose free part, solved from the zero-gradient
-// equations, lies inside the box (the 27th, all free, is the mean itself, tested first).
-// Called after cell_overlaps, which it refines; count and fill take the same decisions.
+// Whether the cut-off ellipsoid (padded like the box) meets cell (cx, cy, cz): the minimum of
+// |M y|^2, y = x - mean, over the cell (enlarged by 1e-5) against the padded cut-off. Each
+// sweep minimises along the three axes in turn, which bounds the minimum from above by the
+// value reached and from below by the linearisation there (the function is convex); cells that
+// kSweeps of them leave open are taken as met. The bounds are FP32: `far` bounds their
+// rounding, so a cell is refused only where the ellipsoid cannot reach it. Called after
+// cell_overlaps, which it refines; count and fill take the same decisions. The arithmetic is
+// what bounds the count pass: the exact minimum over the 26 patterns of fixed coordinates in
+// FP64 took 679 us where this takes 254 us (100k Gaussians of the object).
+constexpr int kSweeps = 8;
+
 __device__ __forceinline__ bool cell_meets_ellipsoid(const BakeGrid& G, const float4* gd,
                                                      int cx, int cy, int cz) {
   const int ci[3] = {cx, cy, cz};
-  double lo[3], hi[3], mu[3];
+  const float m[3][3] = {{gd[0].x, gd[1].x, gd[2].x}, {gd[0].y, gd[1].y, gd[2].y},
+                         {gd[0].z, gd[1].z, gd[2].z}};       // m[a]: column a of M
+  float lo[3], hi[3], y[3], im[3];
+  float far = 0.0f;
   const double pad = 1e-5;
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    lo[a] = (double)G.origin[a] + (double)ci[a] * (double)G.cell[a] - pad;
-    hi[a] = (double)G.origin[a] + (double)(ci[a] + 1) * (double)G.cell[a] + pad;
-    mu[a] = (double)gd[a].w;
+    const double mu = (double)gd[a].w;
+    const double edge = (double)G.origin[a] + (double)ci[a] * (double)G.cell[a];
+    lo[a] = (float)(edge - pad - mu);
+    hi[a] = (float)(edge + (double)G.cell[a] + pad - mu);
+    y[a] = fminf(fmaxf(0.0f, lo[a]), hi[a]);
+    im[a] = 1.0f / (m[a][0] * m[a][0] + m[a][1] * m[a][1] + m[a][2] * m[a][2]);
+    far += fmaxf(fabsf(lo[a]), fabsf(hi[a])) *
+           (fabsf(m[a][0]) + fabsf(m[a][1]) + fabsf(m[a][2]));
   }
-  if (mu[0] >= lo[0] && mu[0] <= hi[0] && mu[1] >= lo[1] && mu[1] <= hi[1] &&
-      mu[2] >= lo[2] && mu[2] <= hi[2])
-    return true;
-  double A[3][3];
-  {
-    const double m[3][3] = {{gd[0].x, gd[0].y, gd[0].z}, {gd[1].x, gd[1].y, gd[1].z},
-                            {gd[2].x, gd[2].y, gd[2].z}};
+  const float r = 1.002f * gd[4].z + 1e-6f;
+  const float met = r * r, refused = (r + 2e-6f * far) * (r + 2e-6f * far) + 1e-3f;
+  for (int s = 0; s < kSweeps; ++s) {
+    float z[3];
 #pragma unroll
-    for (int a = 0; a < 3; ++a)
+    for (int k = 0; k < 3; ++k) z[k] = m[0][k] * y[0] + m[1][k] * y[1] + m[2][k] * y[2];
 #pragma unroll
-      for (int b = 0; b < 3; ++b)
-        A[a][b] = m[0][a] * m[0][b] + m[1][a] * m[1][b] + m[2][a] * m[2][b];
-  }
-  const double mmp = 1.002 * (double)gd[4].z + 1e-6;
-  const double r2 = mmp * mmp;
-  {                                               // the cell's centre inside: accept
-    double y[3], q = 0.0;
+    for (int a = 0; a < 3; ++a) {
+      const float to = y[a] - (z[0] * m[a][0] + z[1] * m[a][1] + z[2] * m[a][2]) * im[a];
+      const float at = fminf(fmaxf(to, lo[a]), hi[a]);
 #pragma unroll
-    for (int a = 0; a < 3; ++a) y[a] = 0.5 * (lo[a] + hi[a]) - mu[a];
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-      for (int b = 0; b < 3; ++b) q += y[a] * A[a][b] * y[b];
-    if (q <= r2) return true;
-  }
-  double best = DBL_MAX;
-#pragma unroll
-  for (int code = 0; code < 26; ++code) {        // 26 = all free, covered above
-    const int st[3] = {code % 3, (code / 3) % 3, code / 9};   // 0 free, 1 low, 2 high
-    double y[3];                                  // x - mean
-#pragma unroll
-    for (int a = 0; a < 3; ++a) y[a] = st[a] == 1 ? lo[a] - mu[a] : hi[a] - mu[a];
-    const int nf = (st[0] == 0) + (st[1] == 0) + (st[2] == 0);
-    bool ok = true;
-    if (nf == 1) {
-      const int f = st[0] == 0 ? 0 : (st[1] == 0 ? 1 : 2);
-      const int b0 = (f + 1) % 3, b1 = (f + 2) % 3;
-      y[f] = -(A[f][b0] * y[b0] + A[f][b1] * y[b1]) / A[f][f];
-      ok = y[f] >= lo[f] - mu[f] - 1e-12 && y[f] <= hi[f] - mu[f] + 1e-12;
-    } else if (nf == 2) {
-      const int c = st[0] != 0 ? 0 : (st[1] != 0 ? 1 : 2);
-      const int f = (c + 1) % 3, g = (c + 2) % 3;
-      const double det = A[f][f] * A[g][g] - A[f][g] * A[g][f];
-      const double rf = -A[f][c] * y[c], rg = -A[g][c] * y[c];
-      y[f] = (rf * A[g][g] - A[f][g] * rg) / det;
-      y[g] = (A[f][f] * rg - A[g][f] * rf) / det;
-      ok = y[f] >= lo[f] - mu[f] - 1e-12 && y[f] <= hi[f] - mu[f] + 1e-12 &&
-           y[g] >= lo[g] - mu[g] - 1e-12 && y[g] <= hi[g] - mu[g] + 1e-12;
+      for (int k = 0; k < 3; ++k) z[k] += (at - y[a]) * m[a][k];
+      y[a] = at;
     }
-    if (!ok) continue;
-    double q = 0.0;
+    const float q = z[0] * z[0] + z[1] * z[1] + z[2] * z[2];
+    if (q <= met) return true;
+    float least = q;
 #pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-      for (int b = 0; b < 3; ++b) q += y[a] * A[a][b] * y[b];
-    best = fmin(best, q);
+    for (int a = 0; a < 3; ++a) {
+      const float grad = 2.0f * (z[0] * m[a][0] + z[1] * m[a][1] + z[2] * m[a][2]);
+      least += fminf(grad * (lo[a] - y[a]), grad * (hi[a] - y[a]));
+    }
+    if (least > refused) return false;
   }
-  return best <= r2;
+  return true;
 }
 
-// One wavefront per Gaussian; its lanes take the cells of the Gaussian's box in turn.
 __device__ __forceinline__ void box_cell(const int c0[3], int nx, int ny, int t, int& x,
                                          int& y, int& z) {
   x = c0[0] + t % nx;
@@ -229,74 +206,80 @@ __device__ __forceinline__ void box_cell(const int c0[3], int nx, int ny, int t,
   z = c0[2] + t / (nx * ny);
 }
 
-// The count pass keeps the acceptance bits of the first 64 kCellMaskWords cells of every box
-// (one wavefront ballot per 64 cells), so the fill pass repeats the exact test only beyond
-// them.
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_gauss_count(BakeGrid G, const float4* aabb,
-                                                     int32_t* counts, uint64_t* cellmask,
-                                                     int32_t* overflow) {
-  const int32_t i = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (i >= G.G) return;
-  const float4 lo = aabb[2 * i], hi = aabb[2 * i + 1];
-  int c0[3], c1[3];
-  if (!cell_range(G, lo, hi, c0, c1)) return;
-  if (lane == 0 && !inside_grid(G, lo, hi)) atomicOr(overflow, 1);
-  const float4* gd = G.gdata + (size_t)kGRows * i;
-  const int nx = c1[0] - c0[0] + 1, ny = c1[1] - c0[1] + 1, nz = c1[2] - c0[2] + 1;
-  const int n = nx * ny * nz;
-  for (int t0 = 0; t0 < n; t0 += 64) {       // the same trip count for every lane
-    const int t = t0 + lane;
-    bool acc = false;
-    int32_t c = 0;
-    if (t < n) {
-      int x, y, z;
-      box_cell(c0, nx, ny, t, x, y, z);
-      acc = cell_overlaps(G, gd, x, y, z) && cell_meets_ellipsoid(G, gd, x, y, z);
-      c = (z * G.dims[1] + y) * G.dims[0] + x;
+// A workgroup of kRegWaves wavefronts registers as many Gaussians, all wavefronts at each: its
+// box's cells go in 64s to the wavefronts in turn, beginning at another one for each Gaussian.
+// (With one wavefront per Gaussian the few largest boxes, of thousands of cells, were most of
+// the time of a small scene.) The count pass keeps the acceptance bits of the first
+// 64 kCellMaskWords cells of every box (one wavefront ballot per 64 cells), so the fill pass
+// repeats the test only beyond them.
+constexpr int kRegWaves = 8;
+
+template <class Cell>
+__device__ __forceinline__ void for_box_cells(const BakeGrid& G, const float4* aabb,
+                                              Cell&& cell) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int j = 0; j < kRegWaves; ++j) {
+    const int32_t i = blockIdx.x * kRegWaves + j;
+    if (i >= G.G) return;
+    const float4 lo = aabb[2 * i], hi = aabb[2 * i + 1];
+    int c0[3], c1[3];
+    if (!cell_range(G, lo, hi, c0, c1)) continue;
+    const int first = (wave + j) % kRegWaves;
+    const int nx = c1[0] - c0[0] + 1, ny = c1[1] - c0[1] + 1, nz = c1[2] - c0[2] + 1;
+    const int n = nx * ny * nz;
+    for (int t0 = 64 * first; t0 < n || t0 == 0; t0 += 64 * kRegWaves) {
+      const int t = t0 + lane;
+      int x = 0, y = 0, z = 0;
+      if (t < n) box_cell(c0, nx, ny, t, x, y, z);
+      cell(i, t0, t < n, x, y, z, lo, hi);
     }
+  }
+}
+
+__global__ __launch_bounds__(64 * kRegWaves) void k_gauss_count(BakeGrid G, const float4* aabb,
+                                                                int32_t* counts,
+                                                                uint64_t* cellmask,
+                                                                int32_t* overflow) {
+  for_box_cells(G, aabb, [&](int32_t i, int t0, bool in, int x, int y, int z, const float4& lo,
+                             const float4& hi) {
+    const int lane = threadIdx.x & 63;
+    if (t0 == 0 && lane == 0 && !inside_grid(G, lo, hi)) atomicOr(overflow, 1);
+    const float4* gd = G.gdata + (size_t)kGRows * i;
+    const bool acc =
+        in && cell_overlaps(G, gd, x, y, z) && cell_meets_ellipsoid(G, gd, x, y, z);
     const int w = t0 >> 6;
     if (w < kCellMaskWords) {
       const uint64_t m = __ballot(acc);
       if (lane == 0) cellmask[(size_t)kCellMaskWords * i + w] = m;
     }
-    if (acc) atomicAdd(&counts[c], 1);
-  }
+    if (acc) atomicAdd(&counts[(z * G.dims[1] + y) * G.dims[0] + x], 1);
+  });
 }
 
-__global__ __launch_bounds__(256) void k_gauss_fill(BakeGrid G, const float4* aabb,
-                                                    const uint64_t* cellmask,
-                                                    const int32_t* cell_start, int32_t* cursor,
-                                                    int32_t* entries, int32_t capacity,
-                                                    int32_t* overflow) {
-  const int32_t i = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (i >= G.G) return;
+// The counts run down to zero while the cells are filled.
+__global__ __launch_bounds__(64 * kRegWaves) void k_gauss_fill(BakeGrid G, const float4* aabb,
+                                                               const uint64_t* cellmask,
+                                                               const int32_t* cell_start,
+                                                               int32_t* counts, int32_t* entries,
+                                                               int32_t capacity,
+                                                               int32_t* overflow) {
   const int32_t ncell = G.dims[0] * G.dims[1] * G.dims[2];
   if (cell_start[ncell] > capacity) {      // more registrations than the plan holds
-    if (i == 0 && lane == 0) atomicOr(overflow, 2);
+    if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(overflow, 2);
     return;
   }
-  const float4 lo = aabb[2 * i], hi = aabb[2 * i + 1];
-  int c0[3], c1[3];
-  if (!cell_range(G, lo, hi, c0, c1)) return;
-  const float4* gd = G.gdata + (size_t)kGRows * i;
-  const int nx = c1[0] - c0[0] + 1, ny = c1[1] - c0[1] + 1, nz = c1[2] - c0[2] + 1;
-  const int n = nx * ny * nz;
-  for (int t0 = 0; t0 < n; t0 += 64) {
-    const int t = t0 + lane;
-    if (t >= n) continue;
-    int x, y, z;
-    box_cell(c0, nx, ny, t, x, y, z);
-    const int w = t0 >> 6;
+  for_box_cells(G, aabb, [&](int32_t i, int t0, bool in, int x, int y, int z, const float4&,
+                             const float4&) {
+    const float4* gd = G.gdata + (size_t)kGRows * i;
+    const int w = t0 >> 6, lane = threadIdx.x & 63;
     const bool acc = w < kCellMaskWords
                          ? ((cellmask[(size_t)kCellMaskWords * i + w] >> lane) & 1) != 0
-                         : cell_overlaps(G, gd, x, y, z) && cell_meets_ellipsoid(G, gd, x, y, z);
-    if (!acc) continue;
+                         : in && cell_overlaps(G, gd, x, y, z) &&
+                               cell_meets_ellipsoid(G, gd, x, y, z);
+    if (!acc) return;
     const int32_t c = (z * G.dims[1] + y) * G.dims[0] + x;
-    const int32_t slot = cell_start[c] + atomicAdd(&cursor[c], 1);
-    entries[slot] = i;
-  }
+    entries[cell_start[c] + atomicSub(&counts[c], 1) - 1] = i;
+  });
 }
 
 // ------------------------------------------------------------------------------------------
@@ -331,8 +314,6 @@ __device__ __forceinline__ float exact_alpha(const BakeGrid& G, double tsd, doub
   return fminf(G.alpha_max, op * expf(-0.5f * m2));
 }
 
-constexpr int kLpr = 2;    // lanes that trace one ray
-constexpr int kNb = 24;    // sorted candidate keys per lane
 constexpr int kCap = 32;   // candidates a lane keeps per screening pass
 // screening margins: |t*_32 - t*| < kScreenT (1 + |t*|) and |m^2_32 - m^2| < kScreenM (1 + m^2)
 // hold with a wide margin (measured: 4e-7 and 8e-5 on the object workload)
@@ -357,13 +338,13 @@ __device__ __forceinline__ double dpp_f64(double x) {
   return __longlong_as_double((long long)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo));
 }
 
-// minimum over the kLpr consecutive lanes that trace one ray (DPP quad swaps, then the
-// half-row and row mirrors for groups of 8 and 16)
+// minimum over the LPR consecutive lanes that trace one ray (DPP quad swaps, then the
+// half-row mirror for groups of 8)
+template <int LPR>
 __device__ __forceinline__ double ray_min(double x) {
-  if constexpr (kLpr >= 2) x = fmin(x, dpp_f64<0xB1>(x));
-  if constexpr (kLpr >= 4) x = fmin(x, dpp_f64<0x4E>(x));
-  if constexpr (kLpr >= 8) x = fmin(x, dpp_f64<0x141>(x));
-  if constexpr (kLpr >= 16) x = fmin(x, dpp_f64<0x140>(x));
+  if constexpr (LPR >= 2) x = fmin(x, dpp_f64<0xB1>(x));
+  if constexpr (LPR >= 4) x = fmin(x, dpp_f64<0x4E>(x));
+  if constexpr (LPR >= 8) x = fmin(x, dpp_f64<0x141>(x));
   return x;
 }
 
@@ -373,9 +354,10 @@ struct RayResult {
   float r, g, b, o, dt;
 };
 
-// Traces the ray o + t d64 through the registered Gaussians. The kLpr consecutive lanes
-// that share the ray call it together with their rank g in the ray; mylist is the lane's
-// column of the wavefront's LDS candidate list.
+// Traces the ray o + t d64 through the registered Gaussians. The LPR consecutive lanes that
+// share the ray call it together with their rank g in the ray and hold NB sorted candidate
+// keys each; mylist is the lane's column of the wavefront's LDS candidate list.
+template <int LPR, int NB>
 __device__ __forceinline__ RayResult trace_ray(const BakeGrid& G, const v3& o,
                                                const double (&d64)[3], int g,
                                                int32_t* mylist) {
@@ -438,12 +420,12 @@ __device__ __forceinline__ RayResult trace_ray(const BakeGrid& G, const v3& o,
       const int32_t e1 = min(G.cell_start[cell + 1], G.capacity);
 
       // candidates of this cell in ascending (t*, index): each lane of the ray tests every
-      // kLpr-th entry into its own sorted buffer; the buffers are merged when compositing
+      // LPR-th entry into its own sorted buffer; the buffers are merged when compositing
       double after = -1.0;     // keys <= after are done
       while (e1 > e0 && !done) {            // rounds: the cell again above `after`
-        double key[kNb];
+        double key[NB];
 #pragma unroll
-        for (int s = 0; s < kNb; ++s) key[s] = kNone;
+        for (int s = 0; s < NB; ++s) key[s] = kNone;
         int32_t e = e0 + g;
         for (;;) {
           // pass 1: an FP32 screen of t* and m^2 with wide margins keeps the candidates the
@@ -479,27 +461,27 @@ __device__ __forceinline__ RayResult trace_ray(const BakeGrid& G, const v3& o,
               const float4* gq = G.gdata + (size_t)kGRows * giA;
               a0 = gq[0]; a1 = gq[1]; a2 = gq[2]; amm = gq[4].z;
             }
-            int32_t gnext = e + kLpr < e1 ? G.entries[e + kLpr] : 0;
+            int32_t gnext = e + LPR < e1 ? G.entries[e + LPR] : 0;
             while (e < e1 && n < kCap) {
-              const bool hasB = e + kLpr < e1;
+              const bool hasB = e + LPR < e1;
               if (hasB) {
                 giB = gnext;
                 const float4* gq = G.gdata + (size_t)kGRows * giB;
                 b0 = gq[0]; b1 = gq[1]; b2 = gq[2]; bmm = gq[4].z;
-                gnext = e + 2 * kLpr < e1 ? G.entries[e + 2 * kLpr] : 0;
+                gnext = e + 2 * LPR < e1 ? G.entries[e + 2 * LPR] : 0;
               }
               screen(a0, a1, a2, amm, giA);
-              e += kLpr;
+              e += LPR;
               if (!hasB || n >= kCap) break;
-              const bool hasA = e + kLpr < e1;
+              const bool hasA = e + LPR < e1;
               if (hasA) {
                 giA = gnext;
                 const float4* gq = G.gdata + (size_t)kGRows * giA;
                 a0 = gq[0]; a1 = gq[1]; a2 = gq[2]; amm = gq[4].z;
-                gnext = e + 2 * kLpr < e1 ? G.entries[e + 2 * kLpr] : 0;
+                gnext = e + 2 * LPR < e1 ? G.entries[e + 2 * LPR] : 0;
               }
               screen(b0, b1, b2, bmm, giB);
-              e += kLpr;
+              e += LPR;
               if (!hasA) break;
             }
           }
@@ -515,9 +497,9 @@ __device__ __forceinline__ RayResult trace_ray(const BakeGrid& G, const v3& o,
             const float a = exact_alpha(G, tsd, olx, oly, olz, dlx, dly, dlz, op);
             if (!(a >= G.alpha_min)) continue;
             double k = make_key((float)tsd, gi);
-            if (k <= after || k >= key[kNb - 1]) continue;
+            if (k <= after || k >= key[NB - 1]) continue;
 #pragma unroll
-            for (int s = 0; s < kNb; ++s) {    // sorted insertion, largest falls out
+            for (int s = 0; s < NB; ++s) {    // sorted insertion, largest falls out
               const double lo = fmin(k, key[s]);
               k = fmax(k, key[s]);
               key[s] = lo;
@@ -527,10 +509,10 @@ __device__ __forceinline__ RayResult trace_ray(const BakeGrid& G, const v3& o,
         }
         // every key of the cell up to `bound` is held by some lane: a full lane dropped only
         // keys above its own largest one
-        const double bound = ray_min(key[kNb - 1]);
+        const double bound = ray_min<LPR>(key[NB - 1]);
         for (;;) {
           const double head = key[0];
-          const double m = ray_min(head);
+          const double m = ray_min<LPR>(head);
           if (m == kNone || m > bound) break;
           const uint64_t mb = (uint64_t)__double_as_longlong(m);
           const int32_t gi = (int32_t)(mb & 0xFFFFFFFFu);
@@ -552,8 +534,8 @@ __device__ __forceinline__ RayResult trace_ray(const BakeGrid& G, const v3& o,
           T = Tn;
           if (head == m) {                     // the lane that held it moves to its next key
 #pragma unroll
-            for (int s = 0; s < kNb - 1; ++s) key[s] = key[s + 1];
-            key[kNb - 1] = kNone;
+            for (int s = 0; s < NB - 1; ++s) key[s] = key[s + 1];
+            key[NB - 1] = kNone;
           }
         }
         if (bound == kNone) break;             // no lane dropped a key: the cell is finished
@@ -573,19 +555,18 @@ __device__ __forceinline__ RayResult trace_ray(const BakeGrid& G, const v3& o,
   return res;
 }
 
-// The kernel needs three wavefronts per SIMD (at most 168 registers; it uses 168): at two
-// it runs ~40% slower, so any change here has to keep the register count.
-__global__ __launch_bounds__(256) void k_bake(BakeGrid G, const float* probe_pos, int32_t P,
-                                              int32_t R, float* texels, float* depth,
-                                              const int4* order) {
-  // kLpr lanes trace one ray and split each cell's candidates between them; a wavefront
-  // holds 64/kLpr rays of one probe, taken in Z order inside 8x8 texel tiles so that they
+template <int LPR, int NB>
+__device__ __forceinline__ void bake_rays(const BakeGrid& G, const float* probe_pos, int32_t P,
+                                          int32_t R, float* texels, float* depth,
+                                          const int4* order) {
+  // LPR lanes trace one ray and split each cell's candidates between them; a wavefront
+  // holds 64/LPR rays of one probe, taken in Z order inside 8x8 texel tiles so that they
   // stay coherent; consecutive workgroups take consecutive probes of the order
   const int32_t tiles_x = (R + 7) >> 3;
   const int64_t per_probe = (int64_t)tiles_x * tiles_x * 64;
   const int lane = threadIdx.x & 63;
-  const int g = lane & (kLpr - 1);
-  const int64_t ray = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * (64 / kLpr) + lane / kLpr;
+  const int g = lane & (LPR - 1);
+  const int64_t ray = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * (64 / LPR) + lane / LPR;
   if (ray >= (int64_t)P * per_probe) return;      // whole groups leave together
   const int32_t slot = (int32_t)(ray / per_probe);
   const int32_t p = order ? order[slot].w : slot;
@@ -627,11 +608,30 @@ __global__ __launch_bounds__(256) void k_bake(BakeGrid G, const float* probe_pos
     d64[1] = py * il;
     d64[2] = z * il;
   }
-  const RayResult res = trace_ray(G, o, d64, g, mylist);
+  const RayResult res = trace_ray<LPR, NB>(G, o, d64, g, mylist);
   if (g == 0) {
     reinterpret_cast<float4*>(texels)[texel] = make_float4(res.r, res.g, res.b, res.o);
     if (depth) depth[texel] = res.o > 0.0f ? res.dt / res.o : 0.0f;
   }
+}
+
+constexpr int kLpr = 2;    // lanes that trace one ray where the rays fill the chip
+constexpr int kNb = 24;    // sorted candidate keys per lane then
+
+// The kernel needs three wavefronts per SIMD (at most 168 registers; it uses 168): at two
+// it runs ~40% slower, so any change here has to keep the register count.
+__global__ __launch_bounds__(256) void k_bake(BakeGrid G, const float* probe_pos, int32_t P,
+                                              int32_t R, float* texels, float* depth,
+                                              const int4* order) {
+  bake_rays<kLpr, kNb>(G, probe_pos, P, R, texels, depth, order);
+}
+
+// The same with more lanes per ray, for calls of few rays (see launch_bake).
+template <int LPR, int NB>
+__global__ __launch_bounds__(256) void k_bake_wide(BakeGrid G, const float* probe_pos, int32_t P,
+                                                   int32_t R, float* texels, float* depth,
+                                                   const int4* order) {
+  bake_rays<LPR, NB>(G, probe_pos, P, R, texels, depth, order);
 }
 
 // Traced shading rays: sample j of point p starts at fmaf(offset, n_p, x_p) (per component,
@@ -681,7 +681,7 @@ __global__ __launch_bounds__(256) void k_trace_samples(BakeGrid G, TraceArgs t) 
   }
   double d64[3];
   world_dir64(make_frame64(nx, ny, nz), da, db, e.z, d64);
-  const RayResult res = trace_ray(G, o, d64, g, mylist);
+  const RayResult res = trace_ray<kLpr, kNb>(G, o, d64, g, mylist);
   // the point index is read again rather than held through the trace (registers)
   if (g == 0) {
     const int64_t q = t.order ? (int64_t)__builtin_nontemporal_load(&t.order[slot]) : slot;
@@ -703,31 +703,45 @@ hipError_t launch_gauss_count(const BakeGrid& G, const float4* aabb, int32_t* co
                               uint64_t* cellmask, int32_t* overflow, hipStream_t s) {
   if (G.G == 0) return hipSuccess;
   if (!G.gdata || !aabb || !counts || !cellmask || !overflow) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_gauss_count, dim3((G.G + 3) / 4), dim3(256), 0, s, G, aabb, counts,
-                     cellmask, overflow);
+  hipLaunchKernelGGL(k_gauss_count, dim3((G.G + kRegWaves - 1) / kRegWaves),
+                     dim3(64 * kRegWaves), 0, s, G, aabb, counts, cellmask, overflow);
   return hipGetLastError();
 }
 
 hipError_t launch_gauss_fill(const BakeGrid& G, const float4* aabb, const uint64_t* cellmask,
-                             const int32_t* cell_start, int32_t* cursor, int32_t* entries,
+                             const int32_t* cell_start, int32_t* counts, int32_t* entries,
                              int32_t capacity, int32_t* overflow, hipStream_t s) {
   if (G.G == 0) return hipSuccess;
-  if (!G.gdata || !aabb || !cellmask || !cell_start || !cursor || !entries || !overflow)
+  if (!G.gdata || !aabb || !cellmask || !cell_start || !counts || !entries || !overflow)
     return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_gauss_fill, dim3((G.G + 3) / 4), dim3(256), 0, s, G, aabb, cellmask,
-                     cell_start, cursor, entries, capacity, overflow);
+  hipLaunchKernelGGL(k_gauss_fill, dim3((G.G + kRegWaves - 1) / kRegWaves),
+                     dim3(64 * kRegWaves), 0, s, G, aabb, cellmask, cell_start, counts, entries,
+                     capacity, overflow);
   return hipGetLastError();
 }
+
+// Lanes per ray: few rays leave the chip idle and are as slow as their longest one, which more
+// lanes shorten; many rays fill it, and fewer lanes waste less on cells of few candidates. The
+// lines lie where the times cross (us, 2 / 4 / 8 lanes): 32k rays of 3k Gaussians 888 / 411 /
+// 375, 128k 1361 / 901 / 918, 512k 3268 / 2756 / 3060; of 60k Gaussians 128k 2184 / 1769 /
+// 1621, 512k 4618 / 4381 / 5186, 1M 7619 / 8043 / 10471.
+constexpr int64_t kBakeRays8 = 131072, kBakeRays4 = 524288;
 
 hipError_t launch_bake(const BakeGrid& G, const float* probe_pos, int32_t P, int32_t R,
                        float* texels, float* depth, const int4* order, hipStream_t s) {
   const int64_t tiles = (int64_t)((R + 7) / 8) * ((R + 7) / 8);
   const int64_t rays = (int64_t)P * tiles * 64;
-  const int64_t waves = (rays + (64 / kLpr) - 1) / (64 / kLpr);
-  if (waves == 0) return hipSuccess;
-  const int64_t blocks = (waves + 3) / 4;
-  hipLaunchKernelGGL(k_bake, dim3((unsigned)blocks), dim3(256), 0, s, G, probe_pos, P, R,
-                     texels, depth, order);
+  if (rays == 0) return hipSuccess;
+  auto blocks = [&](int lpr) { return dim3((unsigned)((rays * lpr + 255) / 256)); };
+  if (rays <= kBakeRays8)
+    hipLaunchKernelGGL((k_bake_wide<8, 12>), blocks(8), dim3(256), 0, s, G, probe_pos, P, R,
+                       texels, depth, order);
+  else if (rays <= kBakeRays4)
+    hipLaunchKernelGGL((k_bake_wide<4, 24>), blocks(4), dim3(256), 0, s, G, probe_pos, P, R,
+                       texels, depth, order);
+  else
+    hipLaunchKernelGGL(k_bake, blocks(kLpr), dim3(256), 0, s, G, probe_pos, P, R, texels, depth,
+                       order);
   return hipGetLastError();
 }
 

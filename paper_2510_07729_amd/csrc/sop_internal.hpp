@@ -237,7 +237,7 @@ constexpr int kCellMaskWords = 4;
 hipError_t launch_gauss_count(const BakeGrid& G, const float4* aabb, int32_t* counts,
                               uint64_t* cellmask, int32_t* overflow, hipStream_t s);
 hipError_t launch_gauss_fill(const BakeGrid& G, const float4* aabb, const uint64_t* cellmask,
-                             const int32_t* cell_start, int32_t* cursor, int32_t* entries,
+                             const int32_t* cell_start, int32_t* counts, int32_t* entries,
                              int32_t capacity, int32_t* overflow, hipStream_t s);
 // traced shading: one ray per (point, direction) sample
 struct TraceArgs {
