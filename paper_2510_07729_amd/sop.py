@@ -17,7 +17,8 @@ from . import _lib as L
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    # the current stream's handle without a Stream object around it
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _ptr(t: Optional[torch.Tensor], dtype=None, what: str = "tensor") -> Optional[int]:
@@ -38,8 +39,9 @@ def _shape(t: Optional[torch.Tensor], shape, what: str, dtype=None) -> None:
     mismatch here would otherwise become an out-of-bounds device access."""
     if t is None:
         return
-    if t.dim() != len(shape) or any(s is not None and int(t.shape[i]) != int(s)
-                                    for i, s in enumerate(shape)):
+    if t.shape != shape and (t.dim() != len(shape) or
+                             any(s is not None and int(t.shape[i]) != int(s)
+                                 for i, s in enumerate(shape))):
         want = "[" + ",".join("*" if s is None else str(int(s)) for s in shape) + "]"
         raise ValueError(f"{what} has shape {list(t.shape)}, expected {want}")
     if dtype is not None and t.dtype != dtype:
@@ -50,7 +52,7 @@ def workspace(nbytes: int, device) -> torch.Tensor:
     """A 256-byte-aligned byte buffer of at least nbytes (the tensor may be larger)."""
     buf = torch.empty(max(int(nbytes), 1) + 256, dtype=torch.uint8, device=device)
     off = (-buf.data_ptr()) % 256
-    return buf[off: off + max(int(nbytes), 1)]
+    return buf if off == 0 else buf[off: off + max(int(nbytes), 1)]
 
 
 # ------------------------------------------------------------------------------------------
@@ -89,6 +91,10 @@ class Points:
 
     def c(self) -> L.sop_points:
         self.check()
+        return self._checked()
+
+    def _checked(self) -> L.sop_points:
+        """c() for a caller that has called check()."""
         f = torch.float32
         s = L.sop_points()
         s.count = self.n
@@ -123,6 +129,10 @@ class Neighbors:
 
     def c(self, n: Optional[int] = None) -> L.sop_neighbors:
         self.check(n)
+        return self._checked()
+
+    def _checked(self) -> L.sop_neighbors:
+        """c() for a caller that has called check()."""
         s = L.sop_neighbors()
         s.k = self.k
         s.order = _ptr(self.order, torch.int32, "order")
@@ -139,8 +149,8 @@ def _maps_shape(tex: torch.Tensor, plan=None) -> None:
                          f"{int(plan.n_probes)} probes")
 
 
-def _maps(tex: torch.Tensor, plan=None) -> L.sop_probe_maps:
-    _maps_shape(tex, plan)
+def _maps(tex: torch.Tensor) -> L.sop_probe_maps:
+    """The maps, whose shape the caller has checked (_maps_shape)."""
     m = L.sop_probe_maps()
     m.res = int(tex.shape[1])
     if tex.dtype == torch.float32:
@@ -266,8 +276,8 @@ def sop_query(plan: Plan, texels: torch.Tensor, pts: Points, dirs: torch.Tensor,
     kk = nb.k if nb is not None else k
     ws = workspace(plan.workspace_size(L.SOP_OP_QUERY, n, kk, D, with_neighbors=nb is not None),
                    dev)
-    m, cp = _maps(texels, plan), pts.c()
-    nbc = nb.c(n) if nb is not None else None
+    m, cp = _maps(texels), pts._checked()
+    nbc = nb._checked() if nb is not None else None
     L.check(plan._lib.sop_query(plan.handle, C.byref(m), C.byref(cp),
                                 C.byref(nbc) if nbc is not None else None,
                                 _ptr(dirs, torch.float32, "dirs"), D, k, radius, Lin.data_ptr(),
@@ -336,8 +346,8 @@ def sop_shade(plan: Plan, texels: torch.Tensor, env: torch.Tensor, pts: Points, 
                                            nb is not None), dev)
     o = shade_opts(n_dirs, kk, seed, radius, rotate_per_point, irr, probs, mix_eps, net,
                    env_sampling, cosine)
-    m, e, cp = _maps(texels, plan), _env(env), pts.c()
-    nbc = nb.c(n) if nb is not None else None
+    m, e, cp = _maps(texels), _env(env), pts._checked()
+    nbc = nb._checked() if nb is not None else None
     L.check(plan._lib.sop_shade(plan.handle, C.byref(m), C.byref(e), C.byref(cp),
                                 C.byref(nbc) if nbc is not None else None, C.byref(o),
                                 _ptr(rgb, torch.float32, "rgb"), ws.data_ptr(), ws.numel(),
@@ -362,8 +372,8 @@ def sop_shade_noalloc(plan: Plan, texels: torch.Tensor, env: torch.Tensor, pts: 
         nb.check(n)
     kk = nb.k if nb is not None else k
     o = shade_opts(n_dirs, kk, seed, radius, rotate_per_point, irradiance)
-    m, e, cp = _maps(texels, plan), _env(env), pts.c()
-    nbc = nb.c(n) if nb is not None else None
+    m, e, cp = _maps(texels), _env(env), pts._checked()
+    nbc = nb._checked() if nb is not None else None
     L.check(plan._lib.sop_shade_noalloc(plan.handle, C.byref(m), C.byref(e), C.byref(cp),
                                         C.byref(nbc) if nbc is not None else None, C.byref(o),
                                         _ptr(out, torch.float32, "out"), _stream()),
@@ -413,8 +423,8 @@ def sop_shade_backward(plan: Plan, texels: torch.Tensor, env: torch.Tensor, pts:
         ws = workspace(plan.workspace_size(L.SOP_OP_SHADE_BACKWARD, n, kk, n_dirs, env.shape[:2],
                                            nb is not None), dev)
     o = shade_opts(n_dirs, kk, seed, radius, rotate_per_point)
-    m, e, cp = _maps(texels, plan), _env(env), pts.c()
-    nbc = nb.c(n) if nb is not None else None
+    m, e, cp = _maps(texels), _env(env), pts._checked()
+    nbc = nb._checked() if nb is not None else None
     g = grad_rgb.contiguous()
     if deterministic:
         et = env.texels if isinstance(env, OctEnv) else env
@@ -464,8 +474,8 @@ def sop_dump_integrand(plan: Plan, texels: torch.Tensor, env: torch.Tensor, pts:
         ws = workspace(plan.workspace_size(L.SOP_OP_DUMP_INTEGRAND, n, kk, 1, env.shape[:2],
                                            nb is not None), dev)
     o = shade_opts(1, kk, seed, radius)
-    m, e, cp = _maps(texels, plan), _env(env), pts.c()
-    nbc = nb.c(n) if nb is not None else None
+    m, e, cp = _maps(texels), _env(env), pts._checked()
+    nbc = nb._checked() if nb is not None else None
     L.check(plan._lib.sop_dump_integrand(
         plan.handle, C.byref(m), C.byref(e), C.byref(cp),
         C.byref(nbc) if nbc is not None else None, C.byref(o), int(samples_per_bin),
@@ -585,7 +595,7 @@ def sop_proposal_infer(mlp: Mlp, pts: Points, logits: bool = False,
     lg = torch.empty((n, L.SOP_MLP_BINS), dtype=torch.float32, device=dev) if logits else None
     if ws is None:
         ws = proposal_workspace(L.SOP_OP_PROPOSAL_INFER, n, dev)
-    mc, cp = mlp.c(), pts.c()
+    mc, cp = mlp.c(), pts._checked()
     L.check(mlp._lib.sop_proposal_infer(C.byref(mc), C.byref(cp), _ptr(probs, torch.float32),
                                         _ptr(lg, torch.float32), ws.data_ptr(), ws.numel(),
                                         _stream()), "sop_proposal_infer")
@@ -615,7 +625,7 @@ def sop_proposal_train_step(mlp: Mlp, pts: Points, targets: torch.Tensor,
     if lr is not None:
         mlp.step += 1
         opt = adam_opts(lr, mlp.step, **adam_kw)
-    mc, cp = mlp.c(), pts.c()
+    mc, cp = mlp.c(), pts._checked()
     L.check(mlp._lib.sop_proposal_train_step(
         C.byref(mc), C.byref(cp), _ptr(targets.contiguous(), torch.float32, "targets"),
         C.byref(opt) if opt is not None else None, _ptr(mlp.m), _ptr(mlp.v),
@@ -738,7 +748,7 @@ def sop_shade_traced(plan: BakePlan, env: torch.Tensor, pts: Points, n_dirs: int
                                                      int(env.shape[1]), int(smp is not None))
         ws = workspace(nbytes, dev)
     o = shade_opts(n_dirs, 1, seed, math.inf, rotate_per_point, irr)
-    e, cp = _env(env), pts.c()
+    e, cp = _env(env), pts._checked()
     L.check(lib.sop_shade_traced(plan.handle, oh, C.byref(e), C.byref(cp), C.byref(o),
                                  float(offset), _ptr(rgb, torch.float32, "rgb"), _ptr(smp),
                                  ws.data_ptr(), ws.numel(), _stream()), "sop_shade_traced")
@@ -782,12 +792,12 @@ def sop_shadow_ratio(plan: Plan, texels: torch.Tensor, env_oct: torch.Tensor, pt
     e = L.sop_env_oct()
     e.res = int(env_oct.shape[0])
     e.texels = _ptr(env_oct, torch.float32, "env_oct")
-    m = _maps(texels, plan)
+    m = _maps(texels)
     cp = L.sop_points()
     cp.count = n
     cp.pos = _ptr(pts.pos, torch.float32, "pos")
     cp.normal = _ptr(pts.normal, torch.float32, "normal")
-    nbc = nb.c(n) if nb is not None else None
+    nbc = nb._checked() if nb is not None else None
     L.check(lib.sop_shadow_ratio(plan.handle, C.byref(m), C.byref(e), C.byref(cp),
                                  C.byref(nbc) if nbc is not None else None, C.byref(o),
                                  _ptr(ratio, torch.float32, "ratio"), ws.data_ptr(), ws.numel(),
