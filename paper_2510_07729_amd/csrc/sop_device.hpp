@@ -216,8 +216,9 @@ struct EnvTaps {
   int vi, vj;    // corner tap before the wrap and the clamp, plus 2 (>= 0)
 };
 
-// The texel is chosen from FP32 angles; the fraction inside it is the FP64 angle between the direction and the texel's reference direction (the direction
-// at cu = i exactly, from a per-call table), through a small-angle arctangent series.
+// The texel is chosen from FP32 angles; the fraction inside it is the FP64 angle between the
+// direction and the texel's reference direction (the direction at cu = i exactly, from a
+// per-call table), through a small-angle arctangent series.
 // Both angles then carry ~1e-16 instead of ~1e-7 error, so bilinear weights (and the
 // gradients they scatter) are exact to FP32 rounding even when a weight is small.
 //   col_ref[i + 1] = (cos, sin) of phi_i = 2 pi (i + 0.5)/W - pi,   i in [-1, W]
@@ -354,7 +355,9 @@ __device__ __forceinline__ Material make_material(float NoV_clamped, v3 albedo, 
   M.one_m_k = 1.0f - M.k;
   M.NoV = NoV_clamped;
   M.g1v = M.NoV / (M.NoV * M.one_m_k + M.k);
-  M.vis = M.a2 * kInvPi * M.g1v / (4.0f * M.NoV);
+  // rounded once: an error here would be the same in every sample of the point
+  M.vis = (float)((double)M.a2 / (4.0 * 3.14159265358979323846 *
+                                  fma((double)M.NoV, (double)M.one_m_k, (double)M.k)));
   return M;
 }
 
@@ -392,13 +395,18 @@ __device__ __forceinline__ BrdfTerms brdf_terms(const Material& M, const HalfGeo
   BrdfTerms T;
   T.one_m = hg.one_m;
   T.NoH2 = hg.NoH2;
-  T.iq = rcp32(fmaf(M.a2, T.NoH2, T.one_m));
-  T.iL = rcp32(fmaf(NoL, M.one_m_k, M.k));
-  T.G1L = NoL * T.iL;
+  const float q = fmaf(M.a2, T.NoH2, T.one_m);
+  T.iq = rcp32(q);
+  const float den = fmaf(NoL, M.one_m_k, M.k);
+  T.iL = rcp32(den);
+  const float G = NoL * T.iL;
+  T.G1L = fmaf(fmaf(-den, G, NoL), T.iL, G);          // NoL / den, correctly rounded
   const float x = 1.0f - hg.VoH;
   const float x2 = x * x;
   T.x5 = x2 * x2 * x;
-  T.spec = (M.vis * T.iq) * T.iq * T.G1L;    // in this order: iq^2 alone may overflow
+  const float spec = (M.vis * T.iq) * T.iq * T.G1L;   // in this order: iq^2 alone may overflow
+  const float e = fmaf(-q, T.iq, 1.0f);               // the rounding of iq, which counts twice
+  T.spec = fmaf(spec, e + e, spec);
   return T;
 }
 
