@@ -131,8 +131,7 @@ struct Fwd {
 };
 
 __device__ __forceinline__ void forward_tile(const float* params, const uint16_t* frags,
-                                             const FeatIn& fi, int lane, Fwd& F, uint16_t* xT,
-                                             int64_t ldT, int64_t col, bool store) {
+                                             const FeatIn& fi, int lane, Fwd& F) {
   const int g = lane >> 4;
 #pragma unroll
   for (int mb = 0; mb < 4; ++mb)
@@ -141,13 +140,6 @@ __device__ __forceinline__ void forward_tile(const float* params, const uint16_t
 #pragma unroll
   for (int kb = 0; kb < 10; ++kb) {        // fully unrolled: fi.x[kb] stays in registers
     const bf16x4 b0 = feature_frag(fi, 2 * kb, g), b1 = feature_frag(fi, 2 * kb + 1, g);
-    if (store) {
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        xT[(size_t)(32 * kb + 4 * g + t) * ldT + col] = (uint16_t)b0[t];
-        xT[(size_t)(32 * kb + 16 + 4 * g + t) * ldT + col] = (uint16_t)b1[t];
-      }
-    }
     const bf16x8 b = cat8(b0, b1);
 #pragma unroll
     for (int mb = 0; mb < 4; ++mb) F.z1[mb] = mfma32(load_frag(frags, kF1 + mb * 10 + kb, lane), b, F.z1[mb]);

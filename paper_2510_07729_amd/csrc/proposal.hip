@@ -63,7 +63,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 #pragma unroll
     for (int c = 0; c < 10; ++c) fi.x[c] = 0.0f;
   Fwd F;
-  forward_tile(a.params, a.frags, fi, lane, F, nullptr, 0, 0, false);
+  forward_tile(a.params, a.frags, fi, lane, F);
   if (valid && a.logits) {
 #pragma unroll
     for (int mb = 0; mb < 16; ++mb)
@@ -79,15 +79,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 }
 
 // ------------------------------------------------------------------------------------------
-// training: forward + cross entropy + backward of one 16-point tile per wavefront.
+// training: forward + cross entropy + backward of one 16-point tile per workgroup.
 // Writes the transposed bf16 operands of the weight-gradient GEMM (zero for padding points)
 // and the tile's bias-gradient column sums and loss, which the weight-gradient kernel adds
 // up in a fixed order (no atomics: a step is deterministic).
+// A batch of 4096 points is 256 tiles, one per compute unit, and a tile is one chain through
+// six layers: what bounds it is the chain, not the arithmetic. Its four wavefronts share every
+// layer (wavefront w has the 16 neurons of block w of the hidden layers and 64 of the bins) and
+// hand the next layer's operands over in LDS: 15 us, 36 with one wavefront per tile.
 // ------------------------------------------------------------------------------------------
 constexpr int kPart = kMlpPart;
+constexpr int kTrainWaves = 4;
 
-// sum over the 16 points: by row operations (96 sums a tile; through the LDS crossbar, four
-// dependent steps each, the kernel took 45 us on 4096 points, now 35)
+// sum over the 16 points: by row operations
 __device__ __forceinline__ float tile_col_sum(float v) {
   v = dpp_add<0xB1>(v);          // quad_perm [1,0,3,2]
   v = dpp_add<0x4E>(v);          // quad_perm [2,3,0,1]
@@ -95,123 +99,167 @@ __device__ __forceinline__ float tile_col_sum(float v) {
   return dpp_add<0x140>(v);      // row_mirror
 }
 
-// One wavefront per workgroup: a batch of 4096 points is 256 of them, one per compute unit.
-__global__ __launch_bounds__(64) void k_mlp_train(MlpArgs a) {
+// stores a block's fragment as rows 16 mb + 4 g + t of a transposed operand
+__device__ __forceinline__ void store_rows(uint16_t* T, int64_t ldT, int64_t col, int row0,
+                                           bf16x4 v) {
+#pragma unroll
+  for (int t = 0; t < 4; ++t) T[(size_t)(row0 + t) * ldT + col] = (uint16_t)v[t];
+}
+
+__global__ __launch_bounds__(64 * kTrainWaves) void k_mlp_train(MlpArgs a) {
+  __shared__ bf16x8s s_x[10][64];                // B operands of the first layer
+  __shared__ bf16x4 s_h1[4][64], s_h2[4][64], s_d3[16][64], s_d2[4][64];
+  __shared__ float s_max[kTrainWaves][16], s_sum[kTrainWaves][16], s_tgt[kTrainWaves][16];
+  __shared__ float s_loss[kTrainWaves];
   const int lane = threadIdx.x & 63, g = lane >> 4, r = lane & 15;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t tile = blockIdx.x;
   const int64_t p0 = tile * 16;
   if (p0 >= a.ldT) return;                        // ldT = batch rounded up to 32
   const int64_t p = p0 + r;
   const bool valid = p < a.n;
-  const int64_t col = p;
+  const float vmask = valid ? 1.0f : 0.0f;
+  const int row0 = 16 * w + 4 * g;                // the lane's rows of the wavefront's block
+  float* part = a.part + tile * kPart;
+  auto operand = [&](const bf16x4 (*v)[64], int kb) {
+    return cat8(v[2 * kb][lane], v[2 * kb + 1][lane]);
+  };
+  // features: scalar kb of the ten
   FeatIn fi;
   if (valid) point_scalars(a.pos, a.nrm, a.view, a.cam, a.ppf, a.rough, a.lo, a.inv2, p, fi);
   else
 #pragma unroll
     for (int c = 0; c < 10; ++c) fi.x[c] = 0.0f;
-  Fwd F;
-  forward_tile(a.params, a.frags, fi, lane, F, a.xT, a.ldT, col, true);
-  const float vmask = valid ? 1.0f : 0.0f;
-  // activations stored transposed (zero for padding points)
 #pragma unroll
-  for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      a.h1T[(size_t)(16 * mb + 4 * g + t) * a.ldT + col] = valid ? (uint16_t)F.h1[mb][t] : 0;
-      a.h2T[(size_t)(16 * mb + 4 * g + t) * a.ldT + col] = valid ? (uint16_t)F.h2[mb][t] : 0;
-    }
-  // softmax, normalised targets, loss, dz3 = (q - t) / B
-  float mx = -INFINITY;
-#pragma unroll
-  for (int mb = 0; mb < 16; ++mb)
-#pragma unroll
-    for (int t = 0; t < 4; ++t) mx = fmaxf(mx, F.z3[mb][t]);
-  mx = point_max(mx);
-  float se = 0.0f, ts = 0.0f;
-  float4 T[16];
-#pragma unroll
-  for (int mb = 0; mb < 16; ++mb) {
-    T[mb] = valid ? *reinterpret_cast<const float4*>(a.targets + (size_t)p * kBins + 16 * mb + 4 * g)
-                  : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    ts += T[mb].x + T[mb].y + T[mb].z + T[mb].w;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) se += expf(F.z3[mb][t] - mx);
+  for (int kb = 0; kb < 10; ++kb) {               // fully unrolled: fi.x[kb] stays in registers
+    if (kb % kTrainWaves != w) continue;
+    const bf16x4 b0 = feature_frag(fi, 2 * kb, g), b1 = feature_frag(fi, 2 * kb + 1, g);
+    store_rows(a.xT, a.ldT, p, 32 * kb + 4 * g, b0);
+    store_rows(a.xT, a.ldT, p, 32 * kb + 16 + 4 * g, b1);
+    s_x[kb][lane] = __builtin_shufflevector(b0, b1, 0, 1, 2, 3, 4, 5, 6, 7);
   }
-  se = point_sum(se);
+  __syncthreads();
+  auto bias = [&](int off) {
+    f32x4 z;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) z[t] = a.params[off + t];
+    return z;
+  };
+  auto relu4 = [](const f32x4& z) {
+    return pack4(fmaxf(z[0], 0.0f), fmaxf(z[1], 0.0f), fmaxf(z[2], 0.0f), fmaxf(z[3], 0.0f));
+  };
+  const bf16x4 none = {0, 0, 0, 0};
+  f32x4 z1 = bias(kOffB1 + row0);
+#pragma unroll
+  for (int kb = 0; kb < 10; ++kb)
+    z1 = mfma32(load_frag(a.frags, kF1 + w * 10 + kb, lane),
+                __builtin_bit_cast(bf16x8, s_x[kb][lane]), z1);
+  const bf16x4 h1 = relu4(z1);
+  s_h1[w][lane] = h1;
+  // activations stored transposed (zero for padding points)
+  store_rows(a.h1T, a.ldT, p, row0, valid ? h1 : none);
+  __syncthreads();
+  f32x4 z2 = bias(kOffB2 + row0);
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb)
+    z2 = mfma32(load_frag(a.frags, kF2 + w * 2 + kb, lane), operand(s_h1, kb), z2);
+  const bf16x4 h2 = relu4(z2);
+  s_h2[w][lane] = h2;
+  store_rows(a.h2T, a.ldT, p, row0, valid ? h2 : none);
+  // the targets are loaded meanwhile
+  float4 T[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    T[i] = valid ? *reinterpret_cast<const float4*>(a.targets + (size_t)p * kBins +
+                                                    16 * (4 * w + i) + 4 * g)
+                 : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  __syncthreads();
+  f32x4 z3[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) z3[i] = bias(kOffB3 + 16 * (4 * w + i) + 4 * g);
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb) {
+    const bf16x8 b = operand(s_h2, kb);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      z3[i] = mfma32(load_frag(a.frags, kF3 + (4 * w + i) * 2 + kb, lane), b, z3[i]);
+  }
+  // softmax, normalised targets, loss, dz3 = (q - t) / B
+  float mx = -INFINITY, ts = 0.0f, se = 0.0f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) mx = fmaxf(mx, z3[i][t]);
+    ts += T[i].x + T[i].y + T[i].z + T[i].w;
+  }
+  mx = point_max(mx);
   ts = point_sum(ts);
+  if (g == 0) {
+    s_max[w][r] = mx;
+    s_tgt[w][r] = ts;
+  }
+  __syncthreads();
+  mx = fmaxf(fmaxf(s_max[0][r], s_max[1][r]), fmaxf(s_max[2][r], s_max[3][r]));
+  ts = (s_tgt[0][r] + s_tgt[1][r]) + (s_tgt[2][r] + s_tgt[3][r]);
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) se += expf(z3[i][t] - mx);
+  se = point_sum(se);
+  if (g == 0) s_sum[w][r] = se;
+  __syncthreads();
+  se = (s_sum[0][r] + s_sum[1][r]) + (s_sum[2][r] + s_sum[3][r]);
   const float lse = mx + logf(se);
   const bool uni = !(ts > 0.0f);
   const float its = uni ? 0.0f : 1.0f / ts;
   const float invB = 1.0f / (float)a.n;
   float loss = 0.0f;
-  bf16x4 d3[16];
 #pragma unroll
-  for (int mb = 0; mb < 16; ++mb) {
-    const float tv[4] = {T[mb].x, T[mb].y, T[mb].z, T[mb].w};
+  for (int i = 0; i < 4; ++i) {
+    const int mb = 4 * w + i;
+    const float tv[4] = {T[i].x, T[i].y, T[i].z, T[i].w};
     float dz[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
       const float tt = uni ? (1.0f / kBins) : tv[t] * its;
-      loss -= tt * (F.z3[mb][t] - lse);
-      dz[t] = (expf(F.z3[mb][t] - lse) - tt) * invB * vmask;
+      loss -= tt * (z3[i][t] - lse);
+      dz[t] = (expf(z3[i][t] - lse) - tt) * invB * vmask;
       const float cs = tile_col_sum(dz[t]);
-      if (r == 0) a.part[tile * kPart + 2 * kHid + 16 * mb + 4 * g + t] = cs;
+      if (r == 0) part[2 * kHid + 16 * mb + 4 * g + t] = cs;
     }
-    d3[mb] = pack4(dz[0], dz[1], dz[2], dz[3]);
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-      a.dz3T[(size_t)(16 * mb + 4 * g + t) * a.ldT + col] = (uint16_t)d3[mb][t];
+    const bf16x4 d3 = pack4(dz[0], dz[1], dz[2], dz[3]);
+    s_d3[mb][lane] = d3;
+    store_rows(a.dz3T, a.ldT, p, 16 * mb + 4 * g, d3);
   }
   loss = wave_sum(loss * vmask);
-  if (lane == 0) a.part[tile * kPart + kPart - 1] = loss * invB;
-  // dh2^T = W3 dz3^T, dz2 = dh2 [z2 > 0]
-  f32x4 acc[4];
-#pragma unroll
-  for (int mb = 0; mb < 4; ++mb) acc[mb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-  for (int kb = 0; kb < 8; ++kb) {
-    const bf16x8 b = cat8(d3[2 * kb], d3[2 * kb + 1]);
-#pragma unroll
-    for (int mb = 0; mb < 4; ++mb) acc[mb] = mfma32(load_frag(a.frags, kB3 + mb * 8 + kb, lane), b, acc[mb]);
-  }
-  bf16x4 d2[4];
-#pragma unroll
-  for (int mb = 0; mb < 4; ++mb) {
+  if (lane == 0) s_loss[w] = loss;
+  __syncthreads();
+  if (threadIdx.x == 0)
+    part[kPart - 1] = ((s_loss[0] + s_loss[1]) + (s_loss[2] + s_loss[3])) * invB;
+  // dh2^T = W3 dz3^T, dz2 = dh2 [z2 > 0]; then dh1^T = W2 dz2^T, dz1 = dh1 [z1 > 0]
+  auto masked = [&](const f32x4& acc, const f32x4& z, int part0) {
     float dz[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      dz[t] = F.z2[mb][t] > 0.0f ? acc[mb][t] : 0.0f;
+      dz[t] = z[t] > 0.0f ? acc[t] : 0.0f;
       const float cs = tile_col_sum(dz[t]);
-      if (r == 0) a.part[tile * kPart + kHid + 16 * mb + 4 * g + t] = cs;
+      if (r == 0) part[part0 + row0 + t] = cs;
     }
-    d2[mb] = pack4(dz[0], dz[1], dz[2], dz[3]);
+    return pack4(dz[0], dz[1], dz[2], dz[3]);
+  };
+  f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
-      a.dz2T[(size_t)(16 * mb + 4 * g + t) * a.ldT + col] = (uint16_t)d2[mb][t];
-  }
-  // dh1^T = W2 dz2^T, dz1 = dh1 [z1 > 0]
+  for (int kb = 0; kb < 8; ++kb)
+    acc = mfma32(load_frag(a.frags, kB3 + w * 8 + kb, lane), operand(s_d3, kb), acc);
+  const bf16x4 d2 = masked(acc, z2, kHid);
+  s_d2[w][lane] = d2;
+  store_rows(a.dz2T, a.ldT, p, row0, d2);
+  __syncthreads();
+  acc = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-  for (int mb = 0; mb < 4; ++mb) acc[mb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-  for (int kb = 0; kb < 2; ++kb) {
-    const bf16x8 b = cat8(d2[2 * kb], d2[2 * kb + 1]);
-#pragma unroll
-    for (int mb = 0; mb < 4; ++mb) acc[mb] = mfma32(load_frag(a.frags, kB2 + mb * 2 + kb, lane), b, acc[mb]);
-  }
-#pragma unroll
-  for (int mb = 0; mb < 4; ++mb) {
-    float dz[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      dz[t] = F.z1[mb][t] > 0.0f ? acc[mb][t] : 0.0f;
-      const float cs = tile_col_sum(dz[t]);
-      if (r == 0) a.part[tile * kPart + 16 * mb + 4 * g + t] = cs;
-    }
-    const bf16x4 d1 = pack4(dz[0], dz[1], dz[2], dz[3]);
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-      a.dz1T[(size_t)(16 * mb + 4 * g + t) * a.ldT + col] = (uint16_t)d1[t];
-  }
+  for (int kb = 0; kb < 2; ++kb)
+    acc = mfma32(load_frag(a.frags, kB2 + w * 2 + kb, lane), operand(s_d2, kb), acc);
+  store_rows(a.dz1T, a.ldT, p, row0, masked(acc, z1, 0));
 }
 
 // ------------------------------------------------------------------------------------------
@@ -315,7 +363,7 @@ hipError_t launch_mlp_infer(const MlpArgs& a, hipStream_t s) {
 hipError_t launch_mlp_train(const MlpArgs& a, hipStream_t s) {
   if (a.n == 0) return hipSuccess;
   const int64_t tiles = a.ldT / 16;
-  hipLaunchKernelGGL(k_mlp_train, dim3((unsigned)tiles), dim3(64), 0, s, a);
+  hipLaunchKernelGGL(k_mlp_train, dim3((unsigned)tiles), dim3(64 * kTrainWaves), 0, s, a);
   // the weight tiles, then 64 columns of bias/loss sums each
   hipLaunchKernelGGL(k_mlp_wgrad, dim3(kWgTiles + (kPart + 63) / 64), dim3(64 * kWgWaves), 0, s,
                      a);

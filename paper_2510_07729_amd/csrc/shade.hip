@@ -1119,7 +1119,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 #pragma unroll
       for (int c = 0; c < 10; ++c) fi.x[c] = 0.0f;
     Fwd F;
-    forward_tile(a.mlp_params, a.mlp_frags, fi, lane, F, nullptr, 0, 0, false);
+    forward_tile(a.mlp_params, a.mlp_frags, fi, lane, F);
     softmax_tile(F.z3);
 #pragma unroll
     for (int mb = 0; mb < 16; ++mb) prob[mb] = F.z3[mb];
