@@ -907,7 +907,7 @@ def place_study(torch, sop, scenes, time_ms, tex) -> dict:
         "workload": "object: 4096 probes from 65,536 surface samples; L_sops on the 4096 "
                     "baked 32x32 maps; L_lam on 200k points",
         "fps_ms": round(t_fps, 3), "fps_picks": 4096, "fps_points": 65536,
-        "fps_hbm_bytes": measured_traffic("k_fps"),
+        "fps_hbm_bytes": measured_traffic("k_fps_rounds"),
         "sops_loss_ms": round(t_sops, 4), "sops_bytes": b_sops,
         "sops_GBps": round(b_sops / (t_sops * 1e-3) / 1e9, 1),
         "sops_hbm_frac": round(b_sops / (t_sops * 1e-3) / 1e9 / PEAK_HBM_GBS, 4),
