@@ -10,6 +10,8 @@
 // direction are formed once and reused for all K probes, and per-point sums are reduced
 // across lanes. The backward pass recomputes every sample instead of storing per-sample
 // fetches.
+#include <type_traits>
+
 #include "mlp_device.hpp"
 #include "sop_device.hpp"
 #include "sop_internal.hpp"
@@ -122,6 +124,76 @@ struct Neighbors<0> {
   }
 };
 
+// What a wavefront's lanes wrote to LDS is seen by all of its lanes.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The list of a run-time K for the kernels whose neighbouring lanes take neighbouring points:
+// read from memory inside the loop, an entry costs a cache line per point of the wavefront
+// for every sample (a line for the whole wavefront where its lanes share a point), so the
+// lists are staged in LDS once, kListRow entries apart so that the rows of neighbouring
+// points lie on distinct banks. 200k points, 4096 probes, S = 64, f32 maps: shading K = 6
+// 0.43 -> 0.28 ms, K = 16 1.17 -> 0.57; shadow ratio K = 16 1.20 -> 0.54 (0.88 and 0.91 with
+// the directions of one point in neighbouring lanes and the lists read from memory).
+constexpr int kListRow = SOP_MAX_K + 1;
+struct LdsNeighbors {
+  const int2* row;                       // probe (-1: dropped), weight bits
+  __device__ __forceinline__ int count(int32_t k) const { return k; }
+  __device__ __forceinline__ int32_t id(int s, const ShadeArgs&, int64_t, int32_t) const {
+    return row[s].x;
+  }
+  __device__ __forceinline__ float wt(int s, const ShadeArgs&, int64_t, int32_t) const {
+    return __int_as_float(row[s].y);
+  }
+};
+template <int KT, int PPW>               // PPW points per wavefront
+constexpr bool kStaged = KT == 0 && PPW > 1;
+template <int KT, int PPW>
+using PointNeighbors = std::conditional_t<kStaged<KT, PPW>, LdsNeighbors, Neighbors<KT>>;
+
+// Every lane of the wavefront calls it; L lanes (rank li) share the point p of a valid lane.
+// With BY_PROBE in ascending probe index (see order_by_probe).
+template <int L, bool BY_PROBE>
+__device__ __forceinline__ void stage_list(const ShadeArgs& a, int64_t p, int32_t k, bool valid,
+                                           int li, int2* row) {
+  constexpr int E = (SOP_MAX_K + L - 1) / L;
+  int2 e[E];
+#pragma unroll
+  for (int u = 0; u < E; ++u) {
+    const int s = li + u * L;
+    if (valid && s < k) {
+      const int32_t id = a.nb_idx[p * k + s];
+      e[u] = make_int2((uint32_t)id < (uint32_t)a.P ? id : -1, __float_as_int(a.nb_w[p * k + s]));
+      row[s] = e[u];
+    }
+  }
+  wave_lds_fence();
+  if constexpr (BY_PROBE) {
+    int at[E];
+#pragma unroll
+    for (int u = 0; u < E; ++u) {
+      const int s = li + u * L;
+      at[u] = -1;
+      if (valid && s < k) {
+        int below = 0;
+        for (int j = 0; j < k; ++j) {
+          const uint32_t other = (uint32_t)row[j].x, own = (uint32_t)e[u].x;
+          below += (other < own || (other == own && j < s)) ? 1 : 0;
+        }
+        at[u] = below;
+      }
+    }
+    wave_lds_fence();
+#pragma unroll
+    for (int u = 0; u < E; ++u)
+      if (at[u] >= 0) row[at[u]] = e[u];
+    wave_lds_fence();
+  }
+}
+
 // per-sample quantities shared by forward and backward
 struct Sample {
   double w64[3];
@@ -191,9 +263,9 @@ __device__ __forceinline__ float pair_swap(float v) {
 // adds its two taps of its own sample and its two taps of the partner's, and the
 // partner's part changes lanes once per sample. The sum per sample is the same (its terms
 // are grouped in two halves instead of one running sum).
-template <int KT, typename TexT, bool EO = false, int PAIR = 0>
-__device__ __forceinline__ void eval_at(const ShadeArgs& a, const PointState& ps,
-                                        const Neighbors<KT>& nb, int32_t k, Sample& s) {
+template <int KT, typename TexT, bool EO = false, int PAIR = 0, typename NB>
+__device__ __forceinline__ void eval_at(const ShadeArgs& a, const PointState& ps, const NB& nb,
+                                        int32_t k, Sample& s) {
   s.et = env_taps_of<EO>(a, s.w64);
   s.Le[0] = s.Le[1] = s.Le[2] = 0.0f;
 #pragma unroll
@@ -368,6 +440,7 @@ template <int KT, typename TexT, bool EO = false, bool COS = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_shade_fwd_cl(ShadeArgs a, int32_t k) {
   constexpr int PPW = 64 / kFwdLanes;
   __shared__ FwdPoint s_pt[kWavesPerBlock][PPW];
+  __shared__ int2 s_list[kStaged<KT, PPW> ? kWavesPerBlock : 1][PPW][kListRow];
   const int lane = threadIdx.x & 63, q = (lane >> 4) * 2 + (lane & 1);
   const int64_t wv = die_block() * kWavesPerBlock + wave_id_uniform();
   if (wv * PPW >= a.n) return;                          // uniform over the wavefront
@@ -376,14 +449,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
   FwdPoint& fp = s_pt[threadIdx.x >> 6][pi];
   bool valid;
   int64_t pidx = 0;
-  Neighbors<KT> nb;
+  PointNeighbors<KT, PPW> nb;
   {
     PointState ps;
     valid = slot < a.n && load_point<false>(a, slot, ps);
     if (valid) {
       pidx = ps.p;
-      nb.load(a, ps.p, k);
-      order_by_probe<KT>(nb);
+      if constexpr (KT > 0) {
+        nb.load(a, ps.p, k);
+        order_by_probe<KT>(nb);
+      }
       if (q == 0) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
@@ -405,9 +480,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
       }
     }
   }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  if constexpr (KT > 0) {
+    wave_lds_fence();
+  } else {
+    int2* row = s_list[threadIdx.x >> 6][pi];
+    stage_list<kFwdLanes, true>(a, pidx, k, valid, q, row);
+    nb.row = row;
+  }
   float acc[3] = {0.0f, 0.0f, 0.0f}, acc_e[3] = {0.0f, 0.0f, 0.0f};
   PointState ps;
   ps.p = pidx;
@@ -762,8 +841,15 @@ __global__ __launch_bounds__(256) void k_shadow_ratio(ShadeArgs a, int32_t k) {
     n64[1] = a.nrm[3 * p + 1];
     n64[2] = a.nrm[3 * p + 2];
   }
-  Neighbors<KT> nb;
-  if (valid) nb.load(a, p, k);
+  __shared__ int2 s_list[kStaged<KT, PPW> ? kWavesPerBlock : 1][PPW][kListRow];
+  PointNeighbors<KT, PPW> nb;
+  if constexpr (kStaged<KT, PPW>) {
+    int2* row = s_list[threadIdx.x >> 6][lane % PPW];
+    stage_list<L, false>(a, p, k, valid, li, row);
+    nb.row = row;
+  } else {
+    if (valid) nb.load(a, p, k);
+  }
   const int kn = KT > 0 ? KT : nb.count(k);
   const bool importance = a.shadow_sampler != 0;
   Frame64 F;
@@ -878,9 +964,15 @@ __global__ __launch_bounds__(256) void k_shade_envis(ShadeArgs a, int32_t k) {
   const bool valid = slot < a.n && load_point<L == 64>(a, slot, ps);
   if (L == 64 && !valid) return;
   float acc[3] = {0.0f, 0.0f, 0.0f}, acc_e[3] = {0.0f, 0.0f, 0.0f};
+  __shared__ int2 s_list[kStaged<KT, PPW> ? kWavesPerBlock : 1][PPW][kListRow];
+  PointNeighbors<KT, PPW> nb;
+  if constexpr (kStaged<KT, PPW>) {
+    int2* row = s_list[threadIdx.x >> 6][lane % PPW];
+    stage_list<L, false>(a, ps.p, k, valid, li, row);
+    nb.row = row;
+  }
   if (valid) {
-    Neighbors<KT> nb;
-    nb.load(a, ps.p, k);
+    if constexpr (!kStaged<KT, PPW>) nb.load(a, ps.p, k);
     const int32_t Re = a.env_res, T = Re * Re;
     const uint64_t C = a.env_prefix[T];
     const uint32_t sh = pcg_hash(a.seed), pi = (uint32_t)ps.p;
@@ -1899,7 +1991,9 @@ template <int KT, bool EO>
 static void launch_fwd_e(const ShadeArgs& a, int32_t k, int32_t format, hipStream_t s) {
   constexpr int per_block = kWavesPerBlock * (64 / kFwdLanes);
   const dim3 grid((unsigned)((a.n + per_block - 1) / per_block));
-  const size_t lds = a.per_point ? kFwdRotLds : 0;
+  constexpr size_t lists =
+      KT > 0 ? 0 : sizeof(int2) * kWavesPerBlock * (64 / kFwdLanes) * kListRow;
+  const size_t lds = a.per_point ? kFwdRotLds - lists : 0;
   if (a.cosine) {
     if (format == SOP_TEXEL_F16)
       hipLaunchKernelGGL((k_shade_fwd_cl<KT, uint2, EO, true>), grid, dim3(256), lds, s, a, k);
