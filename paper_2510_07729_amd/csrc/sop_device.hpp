@@ -337,8 +337,11 @@ struct Material {
   float alpha, a2, k;
   float NoV;     // clamped n.v
   float one_m_k; // 1 - k
-  float g1v;     // Smith G1(NoV)
-  float vis;     // alpha^2 G1(NoV) / (4 pi NoV): the factors of spec that no sample changes
+  // factors of a sample's terms that are the same for every sample of the point, each rounded
+  // once: an error here would not average out over the samples
+  float vis;     // alpha^2 G1(NoV) / (4 pi NoV), of spec
+  float rvis;    // r G1(NoV) / (2 pi NoV), of the roughness derivative
+  float dvis;    // (1 - NoV) G1(NoV) / NoV = -dG1/dk / G1 of the view
 };
 
 // NoV is formed in FP64 by the caller: for grazing views n.v is a small difference of
@@ -354,10 +357,12 @@ __device__ __forceinline__ Material make_material(float NoV_clamped, v3 albedo, 
   M.k = 0.5f * M.alpha;
   M.one_m_k = 1.0f - M.k;
   M.NoV = NoV_clamped;
-  M.g1v = M.NoV / (M.NoV * M.one_m_k + M.k);
-  // rounded once: an error here would be the same in every sample of the point
-  M.vis = (float)((double)M.a2 / (4.0 * 3.14159265358979323846 *
-                                  fma((double)M.NoV, (double)M.one_m_k, (double)M.k)));
+  // pi as float: the sums are multiplied by a float 2 pi / S, whose own rounding it cancels
+  const double den = fma((double)M.NoV, (double)M.one_m_k, (double)M.k);    // NoV / G1(NoV)
+  const double four_pi_den = 4.0 * (double)kPi * den;
+  M.vis = (float)((double)M.a2 / four_pi_den);
+  M.rvis = (float)(2.0 * (double)r / four_pi_den);
+  M.dvis = (float)((1.0 - (double)M.NoV) / den);
   return M;
 }
 
@@ -385,6 +390,7 @@ __device__ __forceinline__ HalfGeom half_geom(const double n[3], const double v[
 
 struct BrdfTerms {
   float iq;                 // 1 / q, q = NoH^2 (alpha^2 - 1) + 1: D = alpha^2 iq^2 / pi
+  float eq;                 // 1 - q iq: iq (1 + eq) is 1 / q without iq's rounding
   float G1L, iL;            // Smith G1(NoL) = NoL iL
   float one_m, NoH2, x5;
   float spec;               // D * G / (4 NoV) (times cos cancels 1/NoL)
@@ -398,15 +404,16 @@ __device__ __forceinline__ BrdfTerms brdf_terms(const Material& M, const HalfGeo
   const float q = fmaf(M.a2, T.NoH2, T.one_m);
   T.iq = rcp32(q);
   const float den = fmaf(NoL, M.one_m_k, M.k);
-  T.iL = rcp32(den);
-  const float G = NoL * T.iL;
-  T.G1L = fmaf(fmaf(-den, G, NoL), T.iL, G);          // NoL / den, correctly rounded
+  const float iL = rcp32(den);
+  T.iL = fmaf(iL, fmaf(-den, iL, 1.0f), iL);          // both correctly rounded
+  const float G = NoL * iL;
+  T.G1L = fmaf(fmaf(-den, G, NoL), iL, G);
   const float x = 1.0f - hg.VoH;
   const float x2 = x * x;
   T.x5 = x2 * x2 * x;
   const float spec = (M.vis * T.iq) * T.iq * T.G1L;   // in this order: iq^2 alone may overflow
-  const float e = fmaf(-q, T.iq, 1.0f);               // the rounding of iq, which counts twice
-  T.spec = fmaf(spec, e + e, spec);
+  T.eq = fmaf(-q, T.iq, 1.0f);
+  T.spec = fmaf(spec, T.eq + T.eq, spec);             // iq counts twice
   return T;
 }
 
