@@ -444,8 +444,8 @@ hipError_t launch_point_order(const ProbeGrid& g, const float* pts, int64_t N,
 // ------------------------------------------------------------------------------------------
 // k nearest probes
 // ------------------------------------------------------------------------------------------
-// A search grows a box of grid cells around its points by one cell a side at a time (the
-// points' own cells and their neighbours first) and stops when the K-th best squared
+// A search grows a box of grid cells around its points (their own cells and the neighbours of
+// those first) and stops when the K-th best squared
 // distance is below that to the nearest cell outside the box. One load per lane fetches the
 // ranges of 64 cells of the box, cells that are further off than the K-th best are dropped,
 // and the probes of the rest are numbered across the lanes and fetched 64 at a time: two
@@ -608,6 +608,13 @@ __device__ __forceinline__ void visit_new_cells(const ProbeGrid& g, const CellBo
   }
 }
 
+// The box grows by a cell at first, and by half its radius from 6 cells on (probes in a volume
+// are found within 5): every growth scans the cells it has visited before as well, so that
+// single steps up to radius r look at r / 4 times the final box. That is what bounds points far
+// from all probes: 200k points of a sphere, 16,384 probes in one place beside it, 254 -> 37 ms
+// (a thread per point that visits each cell once: 123); 300 points 39.7 -> 3.6 ms.
+__device__ __forceinline__ int next_radius(int r) { return r < 6 ? r + 1 : r + r / 2; }
+
 // squared distance from lattice position q to the nearest cell outside the box (~0: none)
 __device__ __forceinline__ uint64_t outside_d2(const CellBox& b, const int q[3], int shift,
                                                int n) {
@@ -663,7 +670,7 @@ __global__ __launch_bounds__(256) void k_knn_wave(ProbeGrid g, const float* pts,
   }
   uint64_t best = ~0ull;             // lane s of every row of 16: the s-th best key
   uint32_t kth = ~0u;                // d^2 of the K-th best
-  for (int r = 1;; ++r) {
+  for (int r = 1;; r = next_radius(r)) {
     box_grow(b, c, c, r, G);
     visit_new_cells(
         g, b, lane, [&]() { return min(kth, lim); },
@@ -761,7 +768,7 @@ __global__ __launch_bounds__(256) void k_knn_dense(ProbeGrid g, const float* pts
       b.lo[a] = 0;
       b.hi[a] = -1;
     }
-    for (int r = 1;; ++r) {
+    for (int r = 1;; r = next_radius(r)) {
       box_grow(b, c0, c1, r, G);
       visit_new_cells(
           g, b, lane,
