@@ -208,6 +208,10 @@ __device__ __forceinline__ void box_cell(const int c0[3], int nx, int ny, int t,
 
 // A workgroup of kRegWaves wavefronts registers as many Gaussians, all wavefronts at each: its
 // box's cells go in 64s to the wavefronts in turn, beginning at another one for each Gaussian.
+// The workgroups take neighbouring Gaussians at the same time, so that the entries of a cell
+// lie nearly in the order of their index: the lanes of a ray then screen records that share
+// cache lines (with a workgroup's Gaussians side by side a cell held them in steps of
+// kRegWaves, and a bake of 3000 overlapping Gaussians took 1.5% longer, one of an object 1%).
 // (With one wavefront per Gaussian the few largest boxes, of thousands of cells, were most of
 // the time of a small scene.) The count pass keeps the acceptance bits of the first
 // 64 kCellMaskWords cells of every box (one wavefront ballot per 64 cells), so the fill pass
@@ -219,7 +223,7 @@ __device__ __forceinline__ void for_box_cells(const BakeGrid& G, const float4* a
                                               Cell&& cell) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (int j = 0; j < kRegWaves; ++j) {
-    const int32_t i = blockIdx.x * kRegWaves + j;
+    const int32_t i = (int32_t)(blockIdx.x + j * gridDim.x);
     if (i >= G.G) return;
     const float4 lo = aabb[2 * i], hi = aabb[2 * i + 1];
     int c0[3], c1[3];
@@ -278,7 +282,7 @@ __global__ __launch_bounds__(64 * kRegWaves) void k_gauss_fill(BakeGrid G, const
                                cell_meets_ellipsoid(G, gd, x, y, z);
     if (!acc) return;
     const int32_t c = (z * G.dims[1] + y) * G.dims[0] + x;
-    entries[cell_start[c] + atomicSub(&counts[c], 1) - 1] = i;
+    entries[cell_start[c + 1] - atomicSub(&counts[c], 1)] = i;
   });
 }
 
