@@ -1006,6 +1006,7 @@ struct sop_bake_plan {
   int32_t* cell_start = nullptr;
   int32_t* entries = nullptr;
   int32_t capacity = 0;
+  double per_ray = 0.0;   // entries in a row of average cells across the grid, at creation
   int32_t* scan_tmp = nullptr;
   int32_t* misc = nullptr;   // [0..5] bounds (ordered ints), [6] n_reg, [7] overflow, [8] ext (float)
   sopk::BakeGrid grid{};
@@ -1169,6 +1170,7 @@ extern "C" sop_status sop_bake_plan_create(const sop_gaussians* g, const sop_bak
   const int64_t cap = (int64_t)total + total / 4 + 1024;
   if (cap > INT32_MAX) return bail(SOP_ERR_UNSUPPORTED, "too many grid registrations");
   pl->capacity = (int32_t)cap;
+  if (pl->ncell > 0) pl->per_ray = total / std::pow((double)pl->ncell, 2.0 / 3.0);
   alloc((void**)&pl->entries, (size_t)pl->capacity * sizeof(int32_t));
   if (e != hipSuccess) return bail(SOP_ERR_OUT_OF_MEMORY, "bake entries allocation");
   G.entries = pl->entries;
@@ -1238,7 +1240,8 @@ extern "C" sop_status sop_bake(const sop_bake_plan* plan, const float* probe_pos
     return fail(SOP_ERR_INVALID_ARGUMENT, "probe_pos/texels NULL or misaligned");
   if (n_probes == 0) return SOP_OK;
   SOP_HIP(sopk::launch_bake(plan->grid, probe_pos, n_probes, res, texels, depth,
-                            order_by ? order_by->qsorted : nullptr, (hipStream_t)stream),
+                            order_by ? order_by->qsorted : nullptr, plan->per_ray,
+                            (hipStream_t)stream),
           "sop_bake");
   return SOP_OK;
 }

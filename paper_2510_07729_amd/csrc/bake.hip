@@ -725,22 +725,38 @@ hipError_t launch_gauss_fill(const BakeGrid& G, const float4* aabb, const uint64
 }
 
 // Lanes per ray: few rays leave the chip idle and are as slow as their longest one, which more
-// lanes shorten; many rays fill it, and fewer lanes waste less on cells of few candidates. The
-// lines lie where the times cross (us, 2 / 4 / 8 lanes): 32k rays of 3k Gaussians 888 / 411 /
-// 375, 128k 1361 / 901 / 918, 512k 3268 / 2756 / 3060; of 60k Gaussians 128k 2184 / 1769 /
-// 1621, 512k 4618 / 4381 / 5186, 1M 7619 / 8043 / 10471.
-constexpr int64_t kBakeRays8 = 131072, kBakeRays4 = 524288;
+// lanes shorten; many rays fill it, and more lanes waste more on cells of few candidates. The
+// lines lie where the times cross, and the fewer candidates a ray meets, the sooner they do.
+// per_ray is the number of entries in a row of average cells across the grid, as counted when
+// the plan was made. Times in us, 2 / 4 / 8 lanes:
+//   per_ray 4 (50 small Gaussians): 32k rays 110 / 96 / 90, 64k 108 / 103 / 112,
+//     128k 118 / 139 / 166, 512k 255 / 340 / 499
+//   102 (1000): 64k 371 / 300 / 267, 128k 439 / 377 / 400, 200k 518 / 509 / 566
+//   310 (1000, overlapping): 128k 931 / 701 / 728, 512k 2185 / 2088 / 2437,
+//     1M 3896 / 3916 / 4665
+//   558 (an object of 3000): 128k 985 / 776 / 777, 512k 2493 / 2445 / 2791,
+//     1M 4422 / 4615 / 5379
+struct BakeLines {
+  int64_t rays8, rays4;     // most rays that take 8 and 4 lanes
+};
+static BakeLines bake_lines(double per_ray) {
+  if (per_ray < 64.0) return {32768, 65536};
+  if (per_ray < 256.0) return {65536, 196608};
+  return {131072, 524288};
+}
 
 hipError_t launch_bake(const BakeGrid& G, const float* probe_pos, int32_t P, int32_t R,
-                       float* texels, float* depth, const int4* order, hipStream_t s) {
+                       float* texels, float* depth, const int4* order, double per_ray,
+                       hipStream_t s) {
   const int64_t tiles = (int64_t)((R + 7) / 8) * ((R + 7) / 8);
   const int64_t rays = (int64_t)P * tiles * 64;
   if (rays == 0) return hipSuccess;
+  const BakeLines lines = bake_lines(per_ray);
   auto blocks = [&](int lpr) { return dim3((unsigned)((rays * lpr + 255) / 256)); };
-  if (rays <= kBakeRays8)
+  if (rays <= lines.rays8)
     hipLaunchKernelGGL((k_bake_wide<8, 12>), blocks(8), dim3(256), 0, s, G, probe_pos, P, R,
                        texels, depth, order);
-  else if (rays <= kBakeRays4)
+  else if (rays <= lines.rays4)
     hipLaunchKernelGGL((k_bake_wide<4, 24>), blocks(4), dim3(256), 0, s, G, probe_pos, P, R,
                        texels, depth, order);
   else

@@ -255,7 +255,8 @@ struct TraceArgs {
 };
 hipError_t launch_trace_samples(const BakeGrid& G, const TraceArgs& t, hipStream_t s);
 hipError_t launch_bake(const BakeGrid& G, const float* probe_pos, int32_t P, int32_t R,
-                       float* texels, float* depth, const int4* order, hipStream_t s);
+                       float* texels, float* depth, const int4* order, double per_ray,
+                       hipStream_t s);
 
 // place.hip --------------------------------------------------------------------------------
 // farthest point sampling of P of M points from `start`, chosen [P], probes out [P,3] =
