@@ -778,13 +778,18 @@ def sop_shadow_ratio(plan: Plan, texels: torch.Tensor, env_oct: torch.Tensor, pt
     kk = nb.k if nb is not None else k
     lib = plan._lib
     if ws is None:
-        # with room for the maps' occlusion channel (and a border) the call copies it out first
         nbytes = lib.sop_shadow_workspace_size(plan.handle, n, kk, int(n_dirs),
                                                int(env_oct.shape[0]), int(nb is not None))
-        if nbytes:
-            nbytes += (int(texels.shape[0]) * (int(texels.shape[1]) + 2) ** 2
-                       * texels.element_size() + 256)
-        ws = workspace(nbytes, dev)
+        # with room for the maps' occlusion channel (and a border) a call of at least as many
+        # samples copies it out first; without it, it reads the maps themselves
+        values = int(texels.shape[0]) * (int(texels.shape[1]) + 2) ** 2
+        if nbytes and n * int(n_dirs) >= values:
+            try:
+                ws = workspace(nbytes + values * texels.element_size() + 256, dev)
+            except torch.OutOfMemoryError:
+                pass
+        if ws is None:
+            ws = workspace(nbytes, dev)
     o = L.sop_shadow_opts()
     o.n_dirs, o.k, o.radius, o.seed = int(n_dirs), int(kk), float(radius), int(seed) & 0xFFFFFFFF
     o.rotate_per_point, o.sampler = int(rotate_per_point), int(sampler)
