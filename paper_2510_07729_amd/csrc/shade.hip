@@ -785,17 +785,20 @@ __device__ __forceinline__ float env_inv_pdf(const double w[3], uint32_t m, uint
   return (float)(12.566370614359172 * (double)C / ((double)m * (double)T));
 }
 
-// The occlusion maps of launch_pack_occ: one thread per value.
+// The occlusion maps of launch_pack_occ: one thread per value, up to kPackBlocks workgroups (a
+// launch holds fewer than 2^32 threads, and 65,536 maps of 256 x 256 have more values).
+constexpr int64_t kPackBlocks = 1 << 20;
 template <typename TexT, typename OccT>
 __global__ __launch_bounds__(256) void k_pack_occ(const TexT* tex, int32_t R, int64_t n, OccT* occ) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
   const int side = R + 2;
-  const int64_t p = i / (side * side);
-  const int v = (int)(i - p * (side * side)), row = v / side, col = v - row * side;
-  int ii, jj;
-  oct_wrap(col - 1, row - 1, R, ii, jj);
-  occ[i] = reinterpret_cast<const OccT*>(tex)[4 * (p * R * R + jj * R + ii) + 3];
+  const int64_t step = (int64_t)gridDim.x * 256;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += step) {
+    const int64_t p = i / (side * side);
+    const int v = (int)(i - p * (side * side)), row = v / side, col = v - row * side;
+    int ii, jj;
+    oct_wrap(col - 1, row - 1, R, ii, jj);
+    occ[i] = reinterpret_cast<const OccT*>(tex)[4 * (p * R * R + jj * R + ii) + 3];
+  }
 }
 
 // two adjacent values of an occlusion map (4-byte or 2-byte aligned)
@@ -2155,7 +2158,7 @@ hipError_t launch_pack_occ(const void* texels, int32_t P, int32_t R, int32_t for
   const int64_t n = (int64_t)occ_map_texels(P, R);
   if (n == 0) return hipSuccess;
   if (!texels || !occ) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)((n + 255) / 256));
+  const dim3 grid((unsigned)std::min<int64_t>((n + 255) / 256, kPackBlocks));
   if (format == SOP_TEXEL_F16)
     hipLaunchKernelGGL((k_pack_occ<uint2, uint16_t>), grid, dim3(256), 0, s,
                        reinterpret_cast<const uint2*>(texels), R, n,
