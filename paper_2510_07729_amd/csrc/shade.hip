@@ -154,9 +154,9 @@ constexpr bool kStaged = KT == 0 && PPW > 1;
 template <int KT, int PPW>
 using PointNeighbors = std::conditional_t<kStaged<KT, PPW>, LdsNeighbors, Neighbors<KT>>;
 
-// Every lane of the wavefront calls it; L lanes (rank li) share the point p of a valid lane.
-// With BY_PROBE in ascending probe index (see order_by_probe).
-template <int L, bool BY_PROBE>
+// The list in ascending probe index (see order_by_probe). Every lane of the wavefront calls it;
+// L lanes (rank li) share the point p of a valid lane.
+template <int L>
 __device__ __forceinline__ void stage_list(const ShadeArgs& a, int64_t p, int32_t k, bool valid,
                                            int li, int2* row) {
   constexpr int E = (SOP_MAX_K + L - 1) / L;
@@ -171,27 +171,25 @@ __device__ __forceinline__ void stage_list(const ShadeArgs& a, int64_t p, int32_
     }
   }
   wave_lds_fence();
-  if constexpr (BY_PROBE) {
-    int at[E];
+  int at[E];
 #pragma unroll
-    for (int u = 0; u < E; ++u) {
-      const int s = li + u * L;
-      at[u] = -1;
-      if (valid && s < k) {
-        int below = 0;
-        for (int j = 0; j < k; ++j) {
-          const uint32_t other = (uint32_t)row[j].x, own = (uint32_t)e[u].x;
-          below += (other < own || (other == own && j < s)) ? 1 : 0;
-        }
-        at[u] = below;
+  for (int u = 0; u < E; ++u) {
+    const int s = li + u * L;
+    at[u] = -1;
+    if (valid && s < k) {
+      int below = 0;
+      for (int j = 0; j < k; ++j) {
+        const uint32_t other = (uint32_t)row[j].x, own = (uint32_t)e[u].x;
+        below += (other < own || (other == own && j < s)) ? 1 : 0;
       }
+      at[u] = below;
     }
-    wave_lds_fence();
-#pragma unroll
-    for (int u = 0; u < E; ++u)
-      if (at[u] >= 0) row[at[u]] = e[u];
-    wave_lds_fence();
   }
+  wave_lds_fence();
+#pragma unroll
+  for (int u = 0; u < E; ++u)
+    if (at[u] >= 0) row[at[u]] = e[u];
+  wave_lds_fence();
 }
 
 // per-sample quantities shared by forward and backward
@@ -484,7 +482,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     wave_lds_fence();
   } else {
     int2* row = s_list[threadIdx.x >> 6][pi];
-    stage_list<kFwdLanes, true>(a, pidx, k, valid, q, row);
+    stage_list<kFwdLanes>(a, pidx, k, valid, q, row);
     nb.row = row;
   }
   float acc[3] = {0.0f, 0.0f, 0.0f}, acc_e[3] = {0.0f, 0.0f, 0.0f};
@@ -758,18 +756,36 @@ __device__ __forceinline__ uint64_t slice_div(uint64_t num, double S, double inv
 // the points of a wavefront are neighbouring lanes, lane = PPW (draw slot) + point, and a
 // gather reads a few cache lines where the draws of one point in neighbouring lanes read
 // one each.
+// Their lists are ordered by probe (see order_by_probe), so that these lanes read the same probe
+// at the same step, unless there are fewer than kOrderDraws draws to earn it. 200k points, 4096
+// probes of 32 x 32, K = 8: the ratio from the maps, S = 16, 0.156 -> 0.127 ms (S = 1 0.074
+// against 0.077), from the occlusion maps, S = 64, 0.243 -> 0.213; relighting, S = 16, 16 points
+// a wavefront, 0.153 -> 0.137.
+constexpr int kOrderDraws = 8;
 template <int PPW>
 __device__ __forceinline__ int64_t sky_slot(int lane) {
   return (die_block() * kWavesPerBlock + wave_id_uniform()) * PPW + lane % PPW;
 }
+// Over the lanes of a point, without the LDS crossbar (1% of a call of one or 16 draws: six sums
+// of four shuffles).
 template <int PPW>
-__device__ __forceinline__ float sky_sum(float v) {      // over the lanes of a point
+__device__ __forceinline__ float sky_sum(float v) {
   if constexpr (PPW == 1) {
     return wave_sum(v);
   } else {
-#pragma unroll
-    for (int o = PPW; o < 64; o <<= 1) v += __shfl_xor(v, o);
-    return v;
+    static_assert(PPW == 4 || PPW == 16, "points of a row of 16 lanes");
+    if constexpr (PPW == 4) {
+      v = dpp_add<0x128>(v);             // row_ror:8, lane ^ 8
+      v = dpp_add<0x124>(v);             // row_ror:4, lane ^ 4 (lanes l and l ^ 8 are equal now)
+    }
+    // with both operands v the swaps leave the even rows in one and the odd in the other, then
+    // the lower half and the upper
+    const uint32_t u = __float_as_uint(v);
+    const auto rows = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    v = __uint_as_float(rows[0]) + __uint_as_float(rows[1]);
+    const uint32_t h = __float_as_uint(v);
+    const auto halves = __builtin_amdgcn_permlane32_swap(h, h, false, false);
+    return __uint_as_float(halves[0]) + __uint_as_float(halves[1]);
   }
 }
 
@@ -848,10 +864,12 @@ __global__ __launch_bounds__(256) void k_shadow_ratio(ShadeArgs a, int32_t k) {
   PointNeighbors<KT, PPW> nb;
   if constexpr (kStaged<KT, PPW>) {
     int2* row = s_list[threadIdx.x >> 6][lane % PPW];
-    stage_list<L, false>(a, p, k, valid, li, row);
+    stage_list<L>(a, p, k, valid, li, row);
     nb.row = row;
-  } else {
-    if (valid) nb.load(a, p, k);
+  } else if (valid) {
+    nb.load(a, p, k);
+    if constexpr (KT > 0 && PPW > 1)
+      if (a.S >= kOrderDraws) order_by_probe<KT>(nb);
   }
   const int kn = KT > 0 ? KT : nb.count(k);
   const bool importance = a.shadow_sampler != 0;
@@ -971,11 +989,13 @@ __global__ __launch_bounds__(256) void k_shade_envis(ShadeArgs a, int32_t k) {
   PointNeighbors<KT, PPW> nb;
   if constexpr (kStaged<KT, PPW>) {
     int2* row = s_list[threadIdx.x >> 6][lane % PPW];
-    stage_list<L, false>(a, ps.p, k, valid, li, row);
+    stage_list<L>(a, ps.p, k, valid, li, row);
     nb.row = row;
   }
   if (valid) {
     if constexpr (!kStaged<KT, PPW>) nb.load(a, ps.p, k);
+    if constexpr (KT > 0 && PPW > 1)
+      if (a.S >= kOrderDraws) order_by_probe<KT>(nb);
     const int32_t Re = a.env_res, T = Re * Re;
     const uint64_t C = a.env_prefix[T];
     const uint32_t sh = pcg_hash(a.seed), pi = (uint32_t)ps.p;
@@ -2083,19 +2103,18 @@ hipError_t launch_env_cdf(const float* env, int32_t T, uint32_t* mass, uint64_t*
   return hipGetLastError();
 }
 
-// Points per wavefront of the sky estimates. Up to 32 draws, a wavefront of one point would
-// leave lanes idle: four points (60k relit points, S = 16: 0.098 ms against 0.166 with one and
-// 0.112 with 16; 60k ground points, S = 16, exact density: 0.15 against 0.20 and 0.15).
-// Above that four points gain cache lines but lose wavefronts, and the estimate that reads
-// whole texels is better off alone: the shadow ratio takes four points from kSkyShared points
-// on (S = 64, one / four / 16 points: 60k 0.184 / 0.188 / 0.184 ms, 150k 0.329 / 0.321 / 0.318; from
-// the maps themselves 500k 1.09 / 1.02 / 1.18), relighting does not (200k points, S = 128:
-// 0.72 / 0.87 / 0.87). Sixteen points pay in large calls whose lanes read little: relighting of
-// few draws (200k points, S = 16, four / 16: 0.208 / 0.188) and the ratio from occlusion maps
-// (500k, S = 16, four / 16 / 64: 0.404 / 0.345 / 0.337; S = 64: 0.795 / 0.715 / 0.732).
-constexpr int64_t kSkyShared = 60000, kSkyMany = 131072;
+// Points per wavefront of the sky estimates, us for 4096 probes of 32 x 32 and K = 8 unless said
+// otherwise. Up to 32 draws, a wavefront of one point would leave lanes idle (60k relit points,
+// S = 16: four 98, one 166): four points, or 16 where there are enough wavefronts left, which
+// is from kSkyRelit points on for relighting (S = 16, four / 16: 60k 68 / 70, 80k 82 / 76, 125k
+// 112 / 99, 200k 160 / 137; S = 1: 60k 54 / 34) and from kSkyMany on for the ratio from the
+// occlusion maps (500k, S = 16: 404 / 345; S = 64: 795 / 715). Above 32 draws relighting, which
+// reads whole texels, takes one (200k, S = 128: one 720, four or 16 870), the ratio four from
+// kSkyShared points on (S = 64, one / four, from the maps: 30k 100 / 97 and half maps 74 / 79,
+// 60k 172 / 160 and 136 / 132; 1024 probes of 24 x 24, 30k 69 / 72).
+constexpr int64_t kSkyShared = 60000, kSkyRelit = 65536, kSkyMany = 131072;
 static int sky_points_relit(const ShadeArgs& a) {
-  return a.S > 32 ? 1 : (a.n >= kSkyMany ? 16 : 4);
+  return a.S > 32 ? 1 : (a.n >= kSkyRelit ? 16 : 4);
 }
 static int sky_points_shadow(const ShadeArgs& a) {
   if (a.occ && a.n >= kSkyMany) return 16;
