@@ -463,14 +463,9 @@ __global__ __launch_bounds__(256) void k_fps_finish(const float* pts, const floa
   }
 }
 
-template <int T>
-static void launch_fps_rounds(const FpsRoundArgs& a, unsigned G, int64_t per, hipStream_t s) {
-  if (per <= 1) hipLaunchKernelGGL((k_fps_rounds<1, T>), dim3(G), dim3(256), 0, s, a);
-  else if (per <= 2) hipLaunchKernelGGL((k_fps_rounds<2, T>), dim3(G), dim3(256), 0, s, a);
-  else if (per <= 4) hipLaunchKernelGGL((k_fps_rounds<4, T>), dim3(G), dim3(256), 0, s, a);
-  else if (per <= 8) hipLaunchKernelGGL((k_fps_rounds<8, T>), dim3(G), dim3(256), 0, s, a);
-  else if (per <= 16) hipLaunchKernelGGL((k_fps_rounds<16, T>), dim3(G), dim3(256), 0, s, a);
-  else hipLaunchKernelGGL((k_fps_rounds<kFpsMaxRegPts, T>), dim3(G), dim3(256), 0, s, a);
+template <int U, int T>
+static void launch_fps_rounds(const FpsRoundArgs& a, unsigned G, hipStream_t s) {
+  hipLaunchKernelGGL((k_fps_rounds<U, T>), dim3(G), dim3(256), 0, s, a);
 }
 
 hipError_t launch_place_probes(const float* pts, const float* nrm, int64_t M, int32_t P,
@@ -509,8 +504,17 @@ hipError_t launch_place_probes(const float* pts, const float* nrm, int64_t M, in
     }
     if (e != hipSuccess) return e;
     const FpsRoundArgs a{pts, M, P, start, rows, fault, chosen};
-    if (T == 8) launch_fps_rounds<8>(a, G, per, s);
-    else launch_fps_rounds<4>(a, G, per, s);
+    // up to 16 workgroups hold at most kFpsPts points per thread, more of them at least as many
+    if (T == 8) {
+      if (per <= 1) launch_fps_rounds<1, 8>(a, G, s);
+      else if (per <= 2) launch_fps_rounds<2, 8>(a, G, s);
+      else launch_fps_rounds<kFpsPts, 8>(a, G, s);
+    } else {
+      if (per <= kFpsPts) launch_fps_rounds<kFpsPts, 4>(a, G, s);
+      else if (per <= 8) launch_fps_rounds<8, 4>(a, G, s);
+      else if (per <= 16) launch_fps_rounds<16, 4>(a, G, s);
+      else launch_fps_rounds<kFpsMaxRegPts, 4>(a, G, s);
+    }
   }
   hipLaunchKernelGGL(k_fps_finish, dim3((unsigned)std::min<int64_t>((P + 255) / 256, 1024)),
                      dim3(256), 0, s, pts, nrm, chosen, fault, P, offset, out);
