@@ -17,8 +17,12 @@ from . import _lib as L
 
 
 def _stream() -> int:
-    # the current stream's handle without a Stream object around it
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    # the current stream's handle, without a Stream object around it where this torch has the
+    # (private) query
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch.cuda.current_device())
 
 
 def _ptr(t: Optional[torch.Tensor], dtype=None, what: str = "tensor") -> Optional[int]:
