@@ -420,8 +420,9 @@ __device__ __forceinline__ void order_by_probe(Neighbors<KT>& nb) {
 // a point in neighbouring lanes instead, a load made 37.5 cache accesses, now 27.5.
 //
 // What a sample reads of its point (frame, view, material) stays in LDS instead of in every
-// one of the 8 lanes' registers: 123 registers and four wavefronts per SIMD instead of 166
-// and three. Where every point has a rotation of its own, neighbouring points share nothing
+// one of the 8 lanes' registers: up to 128 registers and four wavefronts per SIMD instead of
+// 166 and three (the attribute holds the cosine-weighted f32 variant there, which takes 129 if
+// it may: 0.347 -> 0.321 ms for 200k points, S = 64). Where every point has a rotation of its own, neighbouring points share nothing
 // and a fourth wavefront only costs cache (1.17 against 1.03 ms on the object workload), so
 // the launch holds those calls at three by their LDS.
 // 200k points, 4096 probes, S = 128, K = 8: 0.84 -> 0.74 ms; a 1920x1080 frame, half
@@ -435,7 +436,7 @@ struct __attribute__((aligned(16))) FwdPoint {   // 144 bytes: 8 points on disti
 };
 constexpr size_t kFwdRotLds = 45000;  // bytes that leave room for three workgroups per unit
 template <int KT, typename TexT, bool EO = false, bool COS = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_shade_fwd_cl(ShadeArgs a, int32_t k) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_shade_fwd_cl(ShadeArgs a, int32_t k) {
   constexpr int PPW = 64 / kFwdLanes;
   __shared__ FwdPoint s_pt[kWavesPerBlock][PPW];
   __shared__ int2 s_list[kStaged<KT, PPW> ? kWavesPerBlock : 1][PPW][kListRow];
