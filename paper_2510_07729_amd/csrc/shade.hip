@@ -1426,7 +1426,7 @@ __device__ __forceinline__ void sample_adjoint(const ShadeArgs& a, const PointSt
     const float F0 = 0.04f * (1.0f - M.m) + al[c] * M.m;
     const float F = F0 + (1.0f - F0) * bt.x5;
     // the diffuse factor is the same for all samples of the point: rounded once
-    const float dif = (float)((1.0 - (double)M.m) * (double)al[c] / (double)kPi);
+    const float dif = (float)((1.0 - (double)M.m) * (double)al[c] * (1.0 / (double)kPi));
     const float fc = fmaf(dif, s.ct, bt.spec * F);
     const float cm = g[c] * Li;
     ga[c] += cm * ((1.0f - M.m) * kInvPi * s.ct + bt.spec * M.m * om5);

@@ -358,11 +358,11 @@ __device__ __forceinline__ Material make_material(float NoV_clamped, v3 albedo, 
   M.one_m_k = 1.0f - M.k;
   M.NoV = NoV_clamped;
   // pi as float: the sums are multiplied by a float 2 pi / S, whose own rounding it cancels
-  const double den = fma((double)M.NoV, (double)M.one_m_k, (double)M.k);    // NoV / G1(NoV)
-  const double four_pi_den = 4.0 * (double)kPi * den;
-  M.vis = (float)((double)M.a2 / four_pi_den);
-  M.rvis = (float)(2.0 * (double)r / four_pi_den);
-  M.dvis = (float)((1.0 - (double)M.NoV) / den);
+  const double iden = rcp64(fma((double)M.NoV, (double)M.one_m_k, (double)M.k));  // G1(NoV) / NoV
+  constexpr double k4Pi = 1.0 / (4.0 * (double)kPi);
+  M.vis = (float)((double)M.a2 * (k4Pi * iden));
+  M.rvis = (float)(2.0 * (double)r * (k4Pi * iden));
+  M.dvis = (float)((1.0 - (double)M.NoV) * iden);
   return M;
 }
 
