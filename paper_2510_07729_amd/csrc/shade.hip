@@ -261,7 +261,10 @@ __device__ __forceinline__ float pair_swap(float v) {
 // adds its two taps of its own sample and its two taps of the partner's, and the
 // partner's part changes lanes once per sample. The sum per sample is the same (its terms
 // are grouped in two halves instead of one running sum).
-template <int KT, typename TexT, bool EO = false, int PAIR = 0, typename NB>
+// With ROWS the occlusion's two rows of a footprint are added up separately, which halves the
+// roundings of each sum (the gradients of sky and maps carry the factor 1 - O, small where O is
+// close to 1).
+template <int KT, typename TexT, bool EO = false, int PAIR = 0, bool ROWS = false, typename NB>
 __device__ __forceinline__ void eval_at(const ShadeArgs& a, const PointState& ps, const NB& nb,
                                         int32_t k, Sample& s) {
   s.et = env_taps_of<EO>(a, s.w64);
@@ -302,6 +305,7 @@ __device__ __forceinline__ void eval_at(const ShadeArgs& a, const PointState& ps
       const float c2 = odd ? u1 : s.tt.w[2];
       const float c3 = odd ? s.tt.w[3] : u1;
       float4 ev = make_float4(0.0f, 0.0f, 0.0f, 0.0f), od = ev;
+      float ev2 = 0.0f, od2 = 0.0f;
 #pragma unroll
       for (int s2 = 0; s2 < kn; ++s2) {
         const int32_t id = nb.id(s2, a, ps.p, k);
@@ -314,12 +318,21 @@ __device__ __forceinline__ void eval_at(const ShadeArgs& a, const PointState& ps
         ev.x = fmaf(e0, x0.x, fmaf(e2, x2.x, ev.x));
         ev.y = fmaf(e0, x0.y, fmaf(e2, x2.y, ev.y));
         ev.z = fmaf(e0, x0.z, fmaf(e2, x2.z, ev.z));
-        ev.w = fmaf(e0, x0.w, fmaf(e2, x2.w, ev.w));
+        if constexpr (ROWS) {
+          ev.w = fmaf(e0, x0.w, ev.w);
+          ev2 = fmaf(e2, x2.w, ev2);
+          od.w = fmaf(e1, x1.w, od.w);
+          od2 = fmaf(e3, x3.w, od2);
+        } else {
+          ev.w = fmaf(e0, x0.w, fmaf(e2, x2.w, ev.w));
+          od.w = fmaf(e1, x1.w, fmaf(e3, x3.w, od.w));
+        }
         od.x = fmaf(e1, x1.x, fmaf(e3, x3.x, od.x));
         od.y = fmaf(e1, x1.y, fmaf(e3, x3.y, od.y));
         od.z = fmaf(e1, x1.z, fmaf(e3, x3.z, od.z));
-        od.w = fmaf(e1, x1.w, fmaf(e3, x3.w, od.w));
       }
+      ev.w += ev2;
+      od.w += od2;
       const float4 keep = odd ? od : ev, send = odd ? ev : od;
       s.Lin[0] = keep.x + pair_swap<PAIR>(send.x);
       s.Lin[1] = keep.y + pair_swap<PAIR>(send.y);
@@ -360,7 +373,7 @@ __device__ __forceinline__ void eval_sample(const ShadeArgs& a, const PointState
   rotated_dir(a, ps, e, s.w64);
   s.w = mk3((float)s.w64[0], (float)s.w64[1], (float)s.w64[2]);
   s.ct = (float)e.z;
-  eval_at<KT, TexT, EO, 1>(a, ps, nb, k, s);
+  eval_at<KT, TexT, EO, 1, true>(a, ps, nb, k, s);
 }
 
 // Sum over the L lanes of a lane group (L = 64: the whole wavefront, with DPP).
