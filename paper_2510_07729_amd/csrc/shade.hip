@@ -331,8 +331,10 @@ __device__ __forceinline__ void eval_at(const ShadeArgs& a, const PointState& ps
         od.y = fmaf(e1, x1.y, fmaf(e3, x3.y, od.y));
         od.z = fmaf(e1, x1.z, fmaf(e3, x3.z, od.z));
       }
-      ev.w += ev2;
-      od.w += od2;
+      if constexpr (ROWS) {
+        ev.w += ev2;
+        od.w += od2;
+      }
       const float4 keep = odd ? od : ev, send = odd ? ev : od;
       s.Lin[0] = keep.x + pair_swap<PAIR>(send.x);
       s.Lin[1] = keep.y + pair_swap<PAIR>(send.y);
@@ -435,9 +437,9 @@ __device__ __forceinline__ void order_by_probe(Neighbors<KT>& nb) {
 // What a sample reads of its point (frame, view, material) stays in LDS instead of in every
 // one of the 8 lanes' registers: up to 128 registers and four wavefronts per SIMD instead of
 // 166 and three (the attribute holds the cosine-weighted f32 variant there, which takes 129 if
-// it may: 0.347 -> 0.321 ms for 200k points, S = 64). Where every point has a rotation of its own, neighbouring points share nothing
-// and a fourth wavefront only costs cache (1.17 against 1.03 ms on the object workload), so
-// the launch holds those calls at three by their LDS.
+// it may: 0.347 -> 0.321 ms for 200k points, S = 64). Where every point has a rotation of its
+// own, neighbouring points share nothing and a fourth wavefront only costs cache (1.17 against
+// 1.03 ms on the object workload), so the launch holds those calls at three by their LDS.
 // 200k points, 4096 probes, S = 128, K = 8: 0.84 -> 0.74 ms; a 1920x1080 frame, half
 // maps, S = 64: 3.82 -> 2.93 ms. The sum over a point's directions is order-free (Eq. 7); the 8
 // lanes' partial sums meet by shuffles.
@@ -848,8 +850,7 @@ __device__ __forceinline__ float2 load_pair(const __half* o) {
 // ratio is formed after the sums over the point's lanes. Bound by the number of its gathers
 // (the texture unit takes 16 cycles for 64 lanes however little each reads), 32 of ~42 of
 // which are the occlusions of 8 probes: from the occlusion maps (OCC) they are 16 of twice the
-// width. 500k points, S = 64, exact density: 0.92 -> 0.64 ms, and
-// 10 us for the maps.
+// width. 500k points, S = 64, exact density: 0.92 -> 0.58 ms, and 10 us for the maps.
 template <typename TexT> struct OccOf;
 template <> struct OccOf<float4> { using T = float; };
 template <> struct OccOf<uint2> { using T = __half; };
